@@ -51,6 +51,7 @@ struct dg_ctx {
   int32_t* d_wall = nullptr;
   double* d_wall_xy = nullptr;
   double* d_scratch = nullptr;
+  void* d_trace[2] = {nullptr, nullptr};  // face traces of a stage's input and output (null: none)
   double* d_force = nullptr;
   double* d_force_part = nullptr;
   unsigned* d_force_ticket = nullptr;
@@ -78,6 +79,45 @@ DeviceTables ctx_tables(const dg_ctx* c);
 // over-integrated FP64 stage)
 inline int ctx_form(const dg_ctx* c) { return c->overint ? kFormOverint : c->precision; }
 KernelPhysics ctx_phys(const dg_ctx* c, const double vw[2]);
+// The stages of one multi-step call: from face traces where the call has
+// buffers for them (tr), else from the neighbours' states.  begin() takes the
+// call's first state; the last stage of the call leaves no traces.
+struct Stages {
+  int N, form;
+  StageTuning tune;
+  void* tr[2];
+  int in = 0;
+  Stages(const dg_ctx* c, void* tr0, void* tr1) : N(c->N), form(ctx_form(c)), tune(c->tune), tr{tr0, tr1} {}
+  int begin(const DeviceTables& t, const KernelPhysics& ph, const double* U, void* stream, std::string& err) {
+    return tr[0] ? launch_face_traces(N, form, t, ph, U, tr[in], stream, err) : 0;
+  }
+  int run(const DeviceTables& t, const KernelPhysics& ph, const double* Uin, double* Uout, double* K1, int i,
+          double dt, bool last, void* stream, std::string& err) {
+    if (!tr[0]) return launch_stage(N, form, tune, t, ph, Uin, Uout, K1, kRkA[i], kRkB[i], dt, 0, stream, err);
+    const int rc = launch_trace_stage(N, form, tune, t, ph, Uin, Uout, K1, kRkA[i], kRkB[i], dt, tr[in],
+                                      last ? nullptr : tr[in ^ 1], stream, err);
+    in ^= 1;
+    return rc;
+  }
+};
+// Face traces serve the nodal stage of straight-sided meshes: not curved
+// elements (the stage launch evaluates them and their neighbours in FP64 beside
+// the straight tiles), bfloat16 operators or over-integration.
+inline size_t ctx_trace_bytes(const dg_ctx* c) {
+  return c->mesh.celem.empty() ? trace_bytes(c->N, c->precision, c->K) : 0;
+}
+// Whether nsteps steps on K elements (of one mesh or a batch) run from traces:
+// the launch that makes the first ones costs 6 us on a small mesh, which the
+// five stages of a single step win back from about 16,000 elements on (one
+// step at p = 4 FP32: 8,192 elements 59.3 against 56.2 us, 20,480 93.9 against
+// 95.9), in FP64 at p >= 5 always (512 elements 106.8 against 114.2 us).
+inline bool traces_pay(int N, int form, int64_t K, int nsteps) {
+  return nsteps > 1 || K >= 16384 || (form != 2 && N >= 5);
+}
+inline Stages ctx_stages(const dg_ctx* c, int nsteps) {
+  const bool use = c->d_trace[0] && !c->overint && traces_pay(c->N, c->precision, c->K, nsteps);
+  return Stages(c, use ? c->d_trace[0] : nullptr, use ? c->d_trace[1] : nullptr);
+}
 // noalloc.hip: device address of the static scratch array on the current
 // device (looked up once per device); its size in bytes
 int noalloc_scratch_address(double** out, std::string& err);

@@ -14,6 +14,15 @@ constexpr int kGeoStride = 16;   // doubles per element in the geometry table
 // or three at orders 5 and 6, where four elements' 3(p + 1) face nodes each
 // (72, 84) would take two passes over the 64 lanes and three (54, 63) take one.
 constexpr int elements_per_tile(int N) { return (N == 5 || N == 6) ? 3 : 4; }
+// The same for the stage from face traces: at p = 1 eight elements (48 of 64
+// face lanes, two groups of matrix-core rows; against four, 327,680 elements in
+// FP32 76 instead of 125 us a stage, 20,480 10.5 instead of 11.6, 512 the
+// same).  At p = 2 seven (63 lanes) pay on meshes beyond the last-level cache
+// (`large`: 115 instead of 130 us), while below them the longer tile costs more
+// than its lanes give (20,480 elements: 14.2 instead of 12.7 us).
+constexpr int trace_elements_per_tile(int N, bool large) {
+  return N == 1 ? 8 : (N == 2 && large ? 7 : elements_per_tile(N));
+}
 
 // Reference-element operators, row-major, FP64 (built once on K^).
 struct RefOps {
@@ -161,6 +170,19 @@ int launch_stage(int N, int form, const StageTuning& tune, const DeviceTables& t
                  const KernelPhysics& ph, const double* U_in, double* U_out, double* K1, double a,
                  double b, double dt, int rhs_only, void* stream, std::string& err);
 int default_waves(int N, int form);
+
+// trace.hip: the stage from face traces.  A trace array holds four values per
+// face node of every element ([K][3 (p + 1)][4], trace_bytes bytes, 16-byte
+// aligned); 0 bytes: the form has no such stage.  launch_face_traces writes
+// the traces of a state; launch_trace_stage reads those of U_in and, unless
+// tr_out is null, writes those of U_out.  Same results as launch_stage, bit
+// for bit.
+size_t trace_bytes(int N, int form, int64_t K);
+int launch_face_traces(int N, int form, const DeviceTables& t, const KernelPhysics& ph, const double* U,
+                       void* tr, void* stream, std::string& err);
+int launch_trace_stage(int N, int form, const StageTuning& tune, const DeviceTables& t,
+                       const KernelPhysics& ph, const double* U_in, double* U_out, double* K1, double a,
+                       double b, double dt, const void* tr_in, void* tr_out, void* stream, std::string& err);
 
 // Batched stages over many meshes (one launch per stage).
 struct BatchItem {              // one instance, in device memory

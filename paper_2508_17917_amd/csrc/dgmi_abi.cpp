@@ -31,7 +31,7 @@ void free_device(dg_ctx* c) {
   void* ptrs[] = {c->d_geo,  c->d_conn,    c->d_ops,     c->d_frag,       c->d_frag32,
                   c->d_frag16, c->d_wall, c->d_wall_xy, c->d_scratch, c->d_force,
                   c->d_force_part, c->d_force_ticket, c->d_oi, c->d_cfl,
-                  c->d_cslot, c->d_celem, c->d_cnode, c->d_cface, c->d_cP};
+                  c->d_cslot, c->d_celem, c->d_cnode, c->d_cface, c->d_cP, c->d_trace[0], c->d_trace[1]};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (c->h_cfl) (void)hipHostFree(c->h_cfl);
@@ -55,6 +55,7 @@ void free_device(dg_ctx* c) {
   c->d_cnode = nullptr;
   c->d_cface = nullptr;
   c->d_cP = nullptr;
+  c->d_trace[0] = c->d_trace[1] = nullptr;
   c->force_blocks = 0;
   c->dev_ready = false;
 }
@@ -287,6 +288,15 @@ int dg_setup(dg_ctx* c) {
     return e == hipErrorOutOfMemory ? fail(c, DG_ENOMEM, "device allocation failed")
                                     : hip_fail(c, e, "hipMalloc");
   }
+  // face traces of a stage's input and output; without the memory for them the
+  // stages run from the neighbours' states
+  if (const size_t bytes = dgmi::ctx_trace_bytes(c)) {
+    if (hipMalloc(&c->d_trace[0], bytes) != hipSuccess || hipMalloc(&c->d_trace[1], bytes) != hipSuccess) {
+      if (c->d_trace[0]) (void)hipFree(c->d_trace[0]);
+      c->d_trace[0] = c->d_trace[1] = nullptr;
+      (void)hipGetLastError();
+    }
+  }
   // the allocation-free entry point's static array on this device (a lookup,
   // no allocation); left unset if the lookup fails, which that entry point
   // then reports
@@ -403,9 +413,11 @@ int dg_rk_step(dg_ctx* c, double* U, double* K1, double dt, const double v_w[2],
   dgmi::DeviceTables t = tables(c);
   dgmi::KernelPhysics k = kphys(c, v_w);
   double* bufs[2] = {U, c->d_scratch};
+  dgmi::Stages stages = dgmi::ctx_stages(c, 1);
+  rc = stages.begin(t, k, U, stream, err);
+  if (rc != 0) return fail(c, rc, err);
   for (int i = 0; i < 5; ++i) {
-    rc = dgmi::launch_stage(c->N, dgmi::ctx_form(c), c->tune, t, k, bufs[i & 1], bufs[(i + 1) & 1], K1, dgmi::kRkA[i], dgmi::kRkB[i], dt, 0,
-                            stream, err);
+    rc = stages.run(t, k, bufs[i & 1], bufs[(i + 1) & 1], K1, i, dt, i == 4, stream, err);
     if (rc != 0) return fail(c, rc, err);
   }
   size_t bytes = (size_t)c->K * 4 * c->ref.Np * sizeof(double);
@@ -435,14 +447,15 @@ int dg_rk_steps(dg_ctx* c, double* U, double* K1, int nsteps, double dt, const d
   // its own
   const bool fuse = force_dev && walls && !c->overint;
   int cur = 0;
+  dgmi::Stages stages = dgmi::ctx_stages(c, nsteps);
+  if (nsteps > 0 && (rc = stages.begin(t, k, U, stream, err)) != 0) return fail(c, rc, err);
   for (int n = 0; n < nsteps; ++n) {
     for (int i = 0; i < 5; ++i) {
       dgmi::DeviceTables ti = t;
       if (fuse && n > 0 && i == 0) ti.force_parts = true;
       if (fuse && n > 0 && i == 1) ti.force_fin = force_dev + 3 * (int64_t)(n - 1);
-      rc = dgmi::launch_stage(c->N, dgmi::ctx_form(c), c->tune, ti, k, bufs[(cur + i) & 1],
-                              bufs[(cur + i + 1) & 1], K1, dgmi::kRkA[i], dgmi::kRkB[i], dt, 0,
-                              stream, err);
+      rc = stages.run(ti, k, bufs[(cur + i) & 1], bufs[(cur + i + 1) & 1], K1, i, dt,
+                      n == nsteps - 1 && i == 4, stream, err);
       if (rc != 0) return fail(c, rc, err);
     }
     cur ^= 1;

@@ -40,14 +40,17 @@ __global__ void fill_zero_kernel(double* __restrict__ a, int n) {
 }
 
 // Layout of the array for one call: [state K*4*Np][partials 3*blocks][ticket]
+// and, where they still fit, the two face trace arrays of the stages (else the
+// stages run from the neighbours' states, with the same results)
 struct Carve {
   double* state;
   double* part;
   unsigned* ticket;
   size_t doubles;
+  void* trace[2];
 };
 
-Carve carve(double* base, size_t state_doubles, int blocks) {
+Carve carve(double* base, size_t state_doubles, int blocks, size_t trace_bytes) {
   Carve c;
   c.state = base;
   c.part = base + state_doubles;
@@ -56,6 +59,9 @@ Carve carve(double* base, size_t state_doubles, int blocks) {
   t = (t + 31) / 32 * 32;
   c.ticket = (unsigned*)(base + t);
   c.doubles = t + 32;
+  const size_t td = (trace_bytes / sizeof(double) + 31) / 32 * 32;
+  const bool fit = td > 0 && c.doubles + 2 * td <= kScratchDoubles;
+  for (int i = 0; i < 2; ++i) c.trace[i] = fit ? base + c.doubles + i * td : nullptr;
   return c;
 }
 
@@ -107,7 +113,10 @@ extern "C" int dg_rk_steps_noalloc(dg_ctx* c, double* U, double* K1, int nsteps,
   if (nsteps < 0) return dgmi::ctx_fail(c, DG_EINVAL, "nsteps must be non-negative");
   if (!std::isfinite(dt)) return dgmi::ctx_fail(c, DG_EINVAL, "dt is not finite");
   const size_t state_doubles = (size_t)c->K * 4 * c->ref.Np;
-  const Carve cv = carve(c->noalloc_scratch, state_doubles, c->force_blocks);
+  const Carve cv = carve(c->noalloc_scratch, state_doubles, c->force_blocks,
+                         c->overint || !dgmi::traces_pay(c->N, c->precision, c->K, nsteps)
+                             ? 0
+                             : dgmi::ctx_trace_bytes(c));
   if (cv.doubles > kScratchDoubles)
     return dgmi::ctx_fail(c, DG_EINVAL,
                           "state of " + std::to_string(state_doubles * sizeof(double)) +
@@ -128,11 +137,15 @@ extern "C" int dg_rk_steps_noalloc(dg_ctx* c, double* U, double* K1, int nsteps,
   }
   double* bufs[2] = {U, cv.state};
   int cur = 0;
+  dgmi::Stages stages(c, cv.trace[0], cv.trace[1]);
+  if (nsteps > 0) {
+    const int rc = stages.begin(t, k, U, stream, err);
+    if (rc != 0) return dgmi::ctx_fail(c, rc, err);
+  }
   for (int n = 0; n < nsteps; ++n) {
     for (int i = 0; i < 5; ++i) {
-      const int rc = dgmi::launch_stage(c->N, dgmi::ctx_form(c), c->tune, t, k, bufs[(cur + i) & 1],
-                                        bufs[(cur + i + 1) & 1], K1, dgmi::kRkA[i], dgmi::kRkB[i], dt,
-                                        0, stream, err);
+      const int rc = stages.run(t, k, bufs[(cur + i) & 1], bufs[(cur + i + 1) & 1], K1, i, dt,
+                                n == nsteps - 1 && i == 4, stream, err);
       if (rc != 0) return dgmi::ctx_fail(c, rc, err);
     }
     cur ^= 1;

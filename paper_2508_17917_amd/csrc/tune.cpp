@@ -110,7 +110,9 @@ int dg_autotune(dg_ctx* c, const double* U, int reps, const char* cache_path, vo
   const double vw0[2] = {0.0, 0.0};
   const dgmi::KernelPhysics ph = dgmi::ctx_phys(c, vw0);
   std::string err;
+  dgmi::Stages stages = dgmi::ctx_stages(c, 2);
   if (e != hipSuccess) rc = dgmi::ctx_hip_fail(c, e, "hipEventCreate");
+  if (rc == DG_OK && stages.begin(t, ph, U, s, err) != 0) rc = dgmi::ctx_fail(c, DG_EHIP, err);
   if (rc == DG_OK && (e = hipMemsetAsync(K1, 0, bytes, s)) != hipSuccess)
     rc = dgmi::ctx_hip_fail(c, e, "hipMemsetAsync");
   // two sweeps over the shapes, each shape's best time kept: the candidates
@@ -126,10 +128,12 @@ int dg_autotune(dg_ctx* c, const double* U, int reps, const char* cache_path, vo
       tune.waves = w;
       tune.grid = grid;
       // a later RK stage (A_2 != 0), as four of the five are: reads U and K1,
-      // writes scratch and K1
+      // writes scratch and K1 (from face traces, and writing them, where the
+      // steps do)
+      stages.tune = tune;
       auto go = [&]() {
-        return dgmi::launch_stage(c->N, dgmi::ctx_form(c), tune, t, ph, U, c->d_scratch, K1,
-                                  dgmi::kRkA[1], dgmi::kRkB[1], 1e-7, 0, s, err);
+        stages.in = 0;
+        return stages.run(t, ph, U, c->d_scratch, K1, 1, 1e-7, false, s, err);
       };
       for (int r = 0; r < 3 && rc == DG_OK; ++r)
         if (go() != 0) rc = dgmi::ctx_fail(c, DG_EHIP, err);
