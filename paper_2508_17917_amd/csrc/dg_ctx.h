@@ -111,7 +111,11 @@ inline size_t ctx_trace_bytes(const dg_ctx* c) {
 // five stages of a single step win back from about 16,000 elements on (one
 // step at p = 4 FP32: 8,192 elements 59.3 against 56.2 us, 20,480 93.9 against
 // 95.9), in FP64 at p >= 5 always (512 elements 106.8 against 114.2 us).
+// At p = 1 in FP64 the eight-element tile is the longer one where the mesh
+// does not fill the chip (2,560 elements 8.2 against 7.6 us a stage, 8,192 8.6
+// against 9.7).
 inline bool traces_pay(int N, int form, int64_t K, int nsteps) {
+  if (N == 1 && form != 2 && K < 8192) return false;
   return nsteps > 1 || K >= 16384 || (form != 2 && N >= 5);
 }
 inline Stages ctx_stages(const dg_ctx* c, int nsteps) {

@@ -13,10 +13,22 @@
 // gradient equals the vector unit's fused multiply-add chain bit for bit, so
 // both forms of the stage give the same bits (checked in the tests).
 //
-// Per element this costs 32 (p + 1) 3 bytes of trace traffic in FP64, 16 (p +
-// 1) 3 in FP32, and the gradient once more on the matrix cores; it saves the
+// Per element this writes and reads 96 (p + 1) bytes of traces in FP64 (48 in
+// FP32) and forms the gradient once more on the matrix cores; it saves the
 // neighbour's block (4 Np values), 16 Np flops per face node and one of the
-// two norms and viscous fluxes.
+// two norms and viscous fluxes, and with the blocks gone from LDS and the
+// vector unit no longer reading the operator fragments at per-lane addresses,
+// FP64 at p >= 5 runs two waves per SIMD instead of one.
+//
+// Measured against the stage from the neighbours' states, us a stage on 20,480
+// elements (in brackets 327,680): p = 1 FP64 18.2 -> 15.1 (255 -> 137), p = 2 FP64
+// 20.6 -> 17.9 (286 -> 191), p = 4 FP32 18.5 -> 15.9 (228 -> 203) and FP64 25.7 ->
+// 22.1, p = 5 FP32 39 -> 28, p = 6 FP32 37 -> 31.6 and FP64 73 -> 50.  What bounds
+// it: on 20,480 elements the vector unit's issue (about 1,000 instructions a
+// tile, five tiles a SIMD, 85 % of the time three waves are resident) between a
+// launch's 2.5 us and 3,000 cycles of cold first loads; beyond the last-level
+// cache memory (p = 4 FP32: 0.95 GB a stage at 4.5 TB/s, 92 % of a large copy's
+// rate).
 #include <hip/hip_runtime.h>
 
 #include "stage_device.h"
@@ -56,8 +68,11 @@ struct TraceOrder {
   static_assert(!FLAT || G * 16 * RS <= H_SZ, "the residual rows take the face terms' area");
   static constexpr int PAD = RS - Np;
   static constexpr int WAVES = 4;
-  // registers: three waves per SIMD in FP32, two in FP64; where K1 / K0 fit
-  // beside the face pass (p = 3, 4) they are loaded before it
+  // registers: three waves per SIMD in FP32, two in FP64 (four and three spill:
+  // p = 4 FP32 16.4 -> 18.1 us, FP64 22.6 -> 24.6).  K1 / K0 are loaded before the
+  // face pass where they fit beside it (p = 3, 4); at p = 5 in FP32 they spill
+  // there (28 -> 35 us).  The next tile's own data come after the face pass
+  // everywhere (before it: p = 4 FP32 16.4 -> 16.8 us, p = 6 FP64 +2 %).
   static constexpr int MIN_WAVES_EU = sizeof(T) == 4 ? 3 : 2;
   static constexpr bool EARLY_K = N == 3 || N == 4;
 };
