@@ -17,6 +17,13 @@ struct dg_batch {
   std::vector<dg_ctx*> ctx;
   std::vector<int> item_of;           // instance -> item (items sorted by order)
   std::vector<double*> A, B, K1;      // per instance
+  std::vector<void*> tr;              // two face trace arrays per instance, or empty
+  bool large = false;                 // the stages' arrays exceed the last-level cache
+  // whether tr[parity] holds the traces of the batch's own current states (but
+  // for the wall faces, whose traces depend on the step's wall velocity): the
+  // last stage of a step leaves them, any other change of the states voids them
+  bool tr_valid = false;
+  int wall_blocks = 0;                // most workgroups of an instance's wall traces
   std::vector<dgmi::BatchGroup> groups;
   dgmi::BatchItem* d_items = nullptr;
   dgmi::BatchStep* d_steps = nullptr;
@@ -72,6 +79,8 @@ void release(dg_batch* b) {
   for (auto* v : {&b->A, &b->B, &b->K1})
     for (double* p : *v)
       if (p) (void)hipFree(p);
+  for (void* p : b->tr)
+    if (p) (void)hipFree(p);
   void* dev[] = {b->d_items, b->d_steps, b->d_parity, b->d_force, b->d_fitems};
   for (void* p : dev)
     if (p) (void)hipFree(p);
@@ -97,7 +106,9 @@ int plan(dg_batch* b) {
   const int W = b->waves ? b->waves : 4;
   if (W != 2 && W != 4) return bfail(b, DG_EINVAL, "waves per workgroup must be 2 or 4");
   b->plan_waves = W;
-  const int resident = dgmi::batch_resident_blocks(b->form, W);
+  const bool tr = !b->tr.empty();
+  const int resident = tr ? dgmi::batch_trace_resident_blocks(0, b->form, W, b->large)
+                          : dgmi::batch_resident_blocks(b->form, W);
   const int ng = (int)b->groups.size();
   std::vector<int64_t> need(ng), nb(ng);
   double total = 0.0;
@@ -110,7 +121,8 @@ int plan(dg_batch* b) {
     if (b->grid == 1) {
       blocks = need[g];
     } else if (b->mode == 1) {
-      const int res = dgmi::batch_order_resident_blocks(b->groups[g].p, b->form, W);
+      const int res = tr ? dgmi::batch_trace_resident_blocks(b->groups[g].p, b->form, W, b->large)
+                         : dgmi::batch_order_resident_blocks(b->groups[g].p, b->form, W);
       blocks = std::min<int64_t>(need[g], res / 8 * 8);
     } else {
       const double share = b->groups[g].ntiles * tile_cost(b->groups[g].p) / total;
@@ -152,7 +164,16 @@ int launch_stage_i(dg_batch* b, int stage, hipStream_t s) {
   for (size_t l = 0; l < b->launches.size(); ++l) {
     // one launch for all groups, or one per group in a kernel sized for its order
     const dgmi::BatchGroups& G = b->launches[l];
-    int rc = b->mode == 0
+    int rc;
+    if (!b->tr.empty())
+      rc = b->mode == 0 ? dgmi::launch_batch_trace_stage(b->form, b->plan_waves, b->large, b->d_items, b->d_steps,
+                                                         b->d_parity, G, b->launch_blocks[l], stage,
+                                                         dgmi::kRkA[stage], dgmi::kRkB[stage], s, err)
+                        : dgmi::launch_batch_trace_order_stage(
+                              G.g[0].p, b->form, b->plan_waves, b->large, b->d_items, b->d_steps, b->d_parity,
+                              G.g[0], b->launch_blocks[l], stage, dgmi::kRkA[stage], dgmi::kRkB[stage], s, err);
+    else
+      rc = b->mode == 0
                  ? dgmi::launch_batch_stage(b->form, b->plan_waves, b->d_items, b->d_steps,
                                             b->d_parity, G, b->launch_blocks[l], stage,
                                             dgmi::kRkA[stage], dgmi::kRkB[stage], s, err)
@@ -165,9 +186,26 @@ int launch_stage_i(dg_batch* b, int stage, hipStream_t s) {
   return DG_OK;
 }
 
+// The face traces of every instance's state, where the stages run from them.
+int launch_traces(dg_batch* b, hipStream_t s) {
+  std::string err;
+  if (!b->tr.empty())
+    for (const dgmi::BatchGroup& g : b->groups) {
+      const int rc = dgmi::launch_batch_face_traces(b->form, b->large, b->d_items, b->d_steps, b->d_parity, g, s, err);
+      if (rc != 0) return bfail(b, rc, err);
+    }
+  return DG_OK;
+}
+
 int launch_step(dg_batch* b, hipStream_t s) {
+  int rc = DG_OK;
+  if (!b->tr.empty() && b->wall_blocks > 0) {
+    std::string err;
+    rc = dgmi::launch_batch_wall_traces(b->form, b->d_items, b->d_steps, b->d_parity, b->n, b->wall_blocks, s, err);
+    if (rc != 0) return bfail(b, rc, err);
+  }
   for (int i = 0; i < 5; ++i) {
-    int rc = launch_stage_i(b, i, s);
+    rc = launch_stage_i(b, i, s);
     if (rc != DG_OK) return rc;
   }
   return DG_OK;
@@ -310,6 +348,25 @@ static int batch_build(dg_batch* b, dg_ctx* const* ctxs, int n) {
   b->A.assign(n, nullptr);
   b->B.assign(n, nullptr);
   b->K1.assign(n, nullptr);
+  // face traces (bfloat16 operators have none), where the step's extra launch
+  // pays and the memory for them is there
+  int64_t elements = 0, bytes = 0;
+  for (int i = 0; i < n; ++i) {
+    elements += ctxs[i]->K;
+    bytes += dgmi::trace_stage_bytes(ctxs[i]->N, b->form, ctxs[i]->K);
+  }
+  if (b->form <= 2 && elements >= 16384) {
+    b->tr.assign(2 * n, nullptr);
+    for (int i = 0; i < 2 * n; ++i)
+      if (hipMalloc(&b->tr[i], dgmi::trace_bytes(ctxs[i / 2]->N, b->form, ctxs[i / 2]->K)) != hipSuccess) {
+        for (void* p : b->tr)
+          if (p) (void)hipFree(p);
+        b->tr.clear();
+        (void)hipGetLastError();
+        break;
+      }
+    b->large = dgmi::beyond_cache(bytes);
+  }
   for (int j = 0; j < n; ++j) {
     const int i = idx[j];
     dg_ctx* c = ctxs[i];
@@ -329,7 +386,12 @@ static int batch_build(dg_batch* b, dg_ctx* const* ctxs, int n) {
     it.buf[0] = b->A[i];
     it.buf[1] = b->B[i];
     it.K1 = b->K1[i];
-    const int ept = dgmi::elements_per_tile(c->N);
+    it.p = c->N;
+    const int per = 64 / (c->N + 1);  // wall faces per workgroup
+    b->wall_blocks = std::max(b->wall_blocks, ((int)c->mesh.wall_faces.size() + per - 1) / per);
+    it.tr[0] = b->tr.empty() ? nullptr : b->tr[2 * i];
+    it.tr[1] = b->tr.empty() ? nullptr : b->tr[2 * i + 1];
+    const int ept = b->tr.empty() ? dgmi::elements_per_tile(c->N) : dgmi::trace_elements_per_tile(c->N, b->large);
     const int64_t ntiles = (c->K + ept - 1) / ept;
     if (b->groups.empty() || b->groups.back().p != c->N) {
       dgmi::BatchGroup g{};
@@ -372,6 +434,7 @@ int dg_batch_set_state(dg_batch* b, int i, const double* U, void* stream) {
   if (rc != DG_OK) return rc;
   if (!U) return bfail(b, DG_EINVAL, "U is NULL");
   double* dst = b->parity ? b->B[i] : b->A[i];
+  b->tr_valid = false;
   hipError_t e = hipMemcpyAsync(dst, U, state_bytes(b->ctx[i]), hipMemcpyDeviceToDevice,
                                 (hipStream_t)stream);
   return e == hipSuccess ? DG_OK : bhip(b, e, "hipMemcpyAsync");
@@ -395,7 +458,9 @@ int dg_batch_rk_step(dg_batch* b, const double* dt, const double* v_w, void* str
       return bfail(b, DG_EINVAL, "dt or v_w not finite");
   hipStream_t s = (hipStream_t)stream;
   int rc = upload(b, dt, v_w, s);
+  if (rc == DG_OK && !b->tr_valid) rc = launch_traces(b, s);
   if (rc != DG_OK) return rc;
+  b->tr_valid = false;  // until the step is on its way
   if (b->use_graph) {
     if (!b->exec) {
       rc = capture(b);
@@ -408,6 +473,7 @@ int dg_batch_rk_step(dg_batch* b, const double* dt, const double* v_w, void* str
     if (rc != DG_OK) return rc;
   }
   b->parity ^= 1;  // five stages: the state now sits in the other buffer
+  b->tr_valid = !b->tr.empty();
   return DG_OK;
 }
 
@@ -426,6 +492,8 @@ int dg_batch_rk_step_states(dg_batch* b, double* const* U, double* const* K1, co
   }
   hipStream_t s = (hipStream_t)stream;
   int rc = upload(b, dt, v_w, s, U, K1);
+  b->tr_valid = false;
+  if (rc == DG_OK) rc = launch_traces(b, s);
   if (rc != DG_OK) return rc;
   if (b->use_graph) {
     if (!b->exec) {
@@ -555,6 +623,8 @@ int dg_batch_autotune(dg_batch* b, int reps, void* stream, double* best_us) {
   // the other state buffer and K1
   std::vector<double> dt(b->n, 1e-7), vw(2 * b->n, 0.0);
   int rc = upload(b, dt.data(), vw.data(), s);
+  b->tr_valid = false;
+  if (rc == DG_OK) rc = launch_traces(b, s);
   if (rc != DG_OK) return rc;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t e = hipEventCreate(&e0);

@@ -186,10 +186,12 @@ int launch_trace_stage(int N, int form, const StageTuning& tune, const DeviceTab
 
 // Batched stages over many meshes (one launch per stage).
 struct BatchItem {              // one instance, in device memory
+  int p;                        // order
   DeviceTables t;
   KernelPhysics ph;             // v_w is taken from the step parameters
   double* buf[2];               // state ping-pong buffers
   double* K1;
+  void* tr[2];                  // face traces of a stage's input and output, or null
   int64_t tile_begin, tile_end; // its tiles in the numbering of its group
 };
 struct ForceItem {              // one instance's wall force in a batched launch (device memory)
@@ -226,6 +228,27 @@ int launch_batch_order_stage(int N, int form, int waves, const BatchItem* items,
 int launch_batch_stage(int form, int waves, const BatchItem* items, const BatchStep* steps,
                        const int* parity, const BatchGroups& G, int blocks, int stage, double a,
                        double b, void* stream, std::string& err);
+// trace_batch.hip: the same from face traces (items with tr set, tiles of
+// trace_elements_per_tile(N, large) elements; large: the batch's arrays exceed
+// the last-level cache).  launch_batch_face_traces writes the traces of a
+// group's states, stage i of a step of parity par (the index of its state's
+// buffer) reads tr[(par + i) & 1] and writes the other, and with the step's
+// wall velocities launch_batch_wall_traces rewrites those of the wall faces
+// that the step before it left.
+// Resident workgroups with N = 0: of the kernel for all orders.
+bool beyond_cache(int64_t bytes);
+int64_t trace_stage_bytes(int N, int form, int64_t K);
+int batch_trace_resident_blocks(int N, int form, int waves, bool large);
+int launch_batch_face_traces(int form, bool large, const BatchItem* items, const BatchStep* steps,
+                             const int* parity, BatchGroup g, void* stream, std::string& err);
+int launch_batch_wall_traces(int form, const BatchItem* items, const BatchStep* steps, const int* parity,
+                             int n_items, int max_blocks, void* stream, std::string& err);
+int launch_batch_trace_stage(int form, int waves, bool large, const BatchItem* items, const BatchStep* steps,
+                             const int* parity, const BatchGroups& G, int blocks, int stage, double a, double b,
+                             void* stream, std::string& err);
+int launch_batch_trace_order_stage(int N, int form, int waves, bool large, const BatchItem* items,
+                                   const BatchStep* steps, const int* parity, const BatchGroup& g, int blocks,
+                                   int stage, double a, double b, void* stream, std::string& err);
 // one thread per wall face node, 64 per workgroup
 int force_blocks_for(int N, int nwall);
 // the wall forces of `count` instances of order N in one launch of `blocks`

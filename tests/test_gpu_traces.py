@@ -106,3 +106,103 @@ def test_streaming_steps_equal_the_stage_chain(p, precision, n):
     assert torch.equal(got, want) and torch.equal(K1, K1w)
     assert np.array_equal(F.cpu().numpy(), Fw)
     s.close()
+
+
+def _batch_case(torch, orders, meshes, precision, seed):
+    from paper_2508_17917_amd.solver import Batch
+    solvers = [_solver(m, p, precision, 1.0) for p, m in zip(orders, meshes)]
+    states = [_state(torch, s, seed + i) for i, s in enumerate(solvers)]
+    return Batch(solvers), solvers, states
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("orders,sizes", [
+    ((4, 1, 6, 4), ((71, 53), (41, 60), (37, 61), (7, 5))),        # tiles of 4, 8 and 3, two instances of one order
+    ((2, 3, 5), ((61, 61), (47, 51), (45, 53))),
+])
+def test_batch_equals_the_stage_chain(orders, sizes, precision):
+    """A batch large enough for traces (16,384 elements or more), in every
+    launch plan, on its own and on the caller's states, with the wall velocity
+    and time step changing between steps, against dg_rk_stage chains."""
+    torch = _torch()
+    print("[gpu-case] batch traces orders=%s precision=%d" % (orders, precision), flush=True)
+    meshes = [mg.ogrid(a, b, 0.5, 8.0, 1.02) for a, b in sizes]
+    assert sum(2 * a * b for a, b in sizes) >= 16384
+    b, solvers, states = _batch_case(torch, orders, meshes, precision, 3)
+    n = len(solvers)
+    dts = [np.array([1e-6 * (1 + i + k) for i in range(n)]) for k in range(2)]
+    vws = [np.array([[0.01 * i, 0.02 * (k + 1)] for i in range(n)]) for k in range(2)]
+    want = []
+    for i, s in enumerate(solvers):
+        U = states[i]
+        for k in range(2):
+            U, K1, _ = _chain(torch, s, U, 1, float(dts[k][i]), tuple(vws[k][i]))
+        want.append((U, K1))
+    for mode, waves, grid, graph in [(0, 4, 0, 1), (0, 2, 1, 0), (1, 4, 0, 1), (1, 2, 0, 1), (1, 4, 1, 0)]:
+        b.configure(mode, waves, grid, bool(graph))
+        for i in range(n):
+            b.set_state(i, states[i])
+        for k in range(2):
+            b.rk_step(dts[k], vws[k])
+        for i in range(n):
+            assert torch.equal(b.get_state(i), want[i][0]), (mode, waves, grid, graph, i)
+    Us = [u.clone() for u in states]
+    K1s = [torch.full_like(u, 7.0) for u in states]
+    for k in range(2):
+        b.rk_step_states(Us, K1s, dts[k], vws[k])
+    for i in range(n):
+        assert torch.equal(Us[i], want[i][0]) and torch.equal(K1s[i], want[i][1]), i
+    b.close()
+
+
+def test_streaming_batch_equals_the_stage_chain():
+    """Beyond the last-level cache: orders 2 (seven-element tiles) and 6."""
+    torch = _torch()
+    meshes = [mg.ogrid(331, 171, 0.5, 30.0, 1.01), mg.ogrid(131, 143, 0.5, 30.0, 1.01)]
+    b, solvers, states = _batch_case(torch, (2, 6), meshes, 0, 11)
+    K2, K6 = (s.K for s in solvers)
+    assert K2 * 1280 + K6 * 4160 > 256 << 20 and K2 % 7 and K6 % 3
+    print("[gpu-case] streaming batch traces K=%d, %d" % (K2, K6), flush=True)
+    dt, vw = np.array([1e-7, 2e-7]), np.array([[0.0, 0.02], [0.01, 0.0]])
+    for i in range(2):
+        b.set_state(i, states[i])
+    for mode in (0, 1):
+        b.configure(mode, 4, 0, True)
+        for i in range(2):
+            b.set_state(i, states[i])
+        b.rk_step(dt, vw)
+        for i, s in enumerate(solvers):
+            U, _, _ = _chain(torch, s, states[i], 1, float(dt[i]), tuple(vw[i]))
+            assert torch.equal(b.get_state(i), U), (mode, i)
+    b.close()
+
+
+def test_batch_traces_follow_the_states():
+    """The traces a step leaves serve the next one only while the states are
+    those it left: one state replaced, steps on the caller's states and the
+    autotuner in between, the wall velocity changing every step."""
+    torch = _torch()
+    sizes = ((71, 53), (41, 60), (37, 61), (7, 5))
+    meshes = [mg.ogrid(a, c, 0.5, 8.0, 1.02) for a, c in sizes]
+    b, solvers, states = _batch_case(torch, (4, 3, 6, 4), meshes, 2, 21)
+    n = len(solvers)
+    dt = np.full(n, 1e-6)
+    vw = lambda k: np.array([[0.0, 0.01 * (k + i)] for i in range(n)])  # noqa: E731
+    cur = [u.clone() for u in states]
+    for i in range(n):
+        b.set_state(i, cur[i])
+    for k in range(5):
+        if k == 2:
+            cur[1] = states[1] * 1.001
+            b.set_state(1, cur[1])
+        if k == 3:
+            b.autotune(reps=1)
+        if k == 4:
+            b.rk_step_states([u.clone() for u in states], [torch.zeros_like(u) for u in states], dt, vw(9))
+            for i in range(n):
+                b.set_state(i, cur[i])
+        b.rk_step(dt, vw(k))
+        for i, s in enumerate(solvers):
+            cur[i] = _chain(torch, s, cur[i], 1, 1e-6, tuple(vw(k)[i]))[0]
+            assert torch.equal(b.get_state(i), cur[i]), (k, i)
+    b.close()
