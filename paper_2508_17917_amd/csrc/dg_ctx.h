@@ -52,6 +52,7 @@ struct dg_ctx {
   double* d_wall_xy = nullptr;
   double* d_scratch = nullptr;
   void* d_trace[2] = {nullptr, nullptr};  // face traces of a stage's input and output (null: none)
+  size_t trace_size = 0;                  // bytes of each
   double* d_force = nullptr;
   double* d_force_part = nullptr;
   unsigned* d_force_ticket = nullptr;
@@ -100,11 +101,12 @@ struct Stages {
     return rc;
   }
 };
-// Face traces serve the nodal stage of straight-sided meshes: not curved
-// elements (the stage launch evaluates them and their neighbours in FP64 beside
-// the straight tiles), bfloat16 operators or over-integration.
+// Face traces serve straight-sided meshes (the stage launch evaluates curved
+// elements and their neighbours in FP64 beside the straight tiles) in every
+// form but bfloat16 operators.  Over-integration switched on after the set-up
+// finds arrays of the nodal size and runs without them.
 inline size_t ctx_trace_bytes(const dg_ctx* c) {
-  return c->mesh.celem.empty() ? trace_bytes(c->N, c->precision, c->K) : 0;
+  return c->mesh.celem.empty() ? trace_bytes(c->N, ctx_form(c), c->K) : 0;
 }
 // Whether nsteps steps on K elements (of one mesh or a batch) run from traces:
 // the launch that makes the first ones costs 6 us on a small mesh, which the
@@ -115,11 +117,13 @@ inline size_t ctx_trace_bytes(const dg_ctx* c) {
 // does not fill the chip (2,560 elements 8.2 against 7.6 us a stage, 8,192 8.6
 // against 9.7).
 inline bool traces_pay(int N, int form, int64_t K, int nsteps) {
+  if (form == kFormOverint) return true;
   if (N == 1 && form != 2 && K < 8192) return false;
   return nsteps > 1 || K >= 16384 || (form != 2 && N >= 5);
 }
 inline Stages ctx_stages(const dg_ctx* c, int nsteps) {
-  const bool use = c->d_trace[0] && !c->overint && traces_pay(c->N, c->precision, c->K, nsteps);
+  const size_t need = ctx_trace_bytes(c);
+  const bool use = need > 0 && need <= c->trace_size && traces_pay(c->N, ctx_form(c), c->K, nsteps);
   return Stages(c, use ? c->d_trace[0] : nullptr, use ? c->d_trace[1] : nullptr);
 }
 // noalloc.hip: device address of the static scratch array on the current

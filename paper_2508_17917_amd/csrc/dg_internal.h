@@ -184,6 +184,14 @@ int launch_trace_stage(int N, int form, const StageTuning& tune, const DeviceTab
                        const KernelPhysics& ph, const double* U_in, double* U_out, double* K1, double a,
                        double b, double dt, const void* tr_in, void* tr_out, void* stream, std::string& err);
 
+// oi_trace.hip: their over-integrated forms (form kFormOverint of the above;
+// traces [K][3q][8] doubles)
+int launch_oi_face_traces(int N, const DeviceTables& t, const KernelPhysics& ph, const double* U, void* tr,
+                          void* stream, std::string& err);
+int launch_oi_trace_stage(int N, const StageTuning& tune, const DeviceTables& t, const KernelPhysics& ph,
+                          const double* U_in, double* U_out, double* K1, double a, double b, double dt,
+                          const void* tr_in, void* tr_out, void* stream, std::string& err);
+
 // Batched stages over many meshes (one launch per stage).
 struct BatchItem {              // one instance, in device memory
   int p;                        // order

@@ -56,6 +56,7 @@ void free_device(dg_ctx* c) {
   c->d_cface = nullptr;
   c->d_cP = nullptr;
   c->d_trace[0] = c->d_trace[1] = nullptr;
+  c->trace_size = 0;
   c->force_blocks = 0;
   c->dev_ready = false;
 }
@@ -295,6 +296,8 @@ int dg_setup(dg_ctx* c) {
       if (c->d_trace[0]) (void)hipFree(c->d_trace[0]);
       c->d_trace[0] = c->d_trace[1] = nullptr;
       (void)hipGetLastError();
+    } else {
+      c->trace_size = bytes;
     }
   }
   // the allocation-free entry point's static array on this device (a lookup,

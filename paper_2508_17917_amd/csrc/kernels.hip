@@ -912,31 +912,6 @@ stage_kernel(DeviceTables t, KernelPhysics ph, const double* __restrict__ Uin,
 // The operator fragments are read from global memory (L2-resident); only the
 // face-point derivative rows sit in LDS.
 template <int N>
-struct OIOrder {
-  using O = Order<N, double>;
-  static constexpr int Np = O::Np, Nfp = O::Nfp, S = O::S, NT = O::NT, KS = O::KS, RS = O::RS;
-  static constexpr int q = oi_points(N), Nq = q * q, NG = 3 * q;
-  static constexpr int NQT = (Nq + 15) / 16;   // 16-point chunks of the element rule
-  static constexpr int KQ = (Nq + 3) / 4;      // k-steps over the element points
-  static constexpr int KG = (NG + 3) / 4;      // k-steps over the face points
-  static constexpr int EPT = (64 / NG) < 4 ? ((64 / NG) > 0 ? 64 / NG : 1) : 4;
-  static constexpr int FRS = 17;               // padded LDS row of one flux chunk
-  static constexpr int GRS = 4 * KG + 1;       // padded LDS row of the face terms
-  static constexpr int U_SZ = 16 * RS, F_SZ = 32 * FRS;
-  static constexpr int N_SZ = 12 * S, H_SZ = 48 * GRS;
-  static constexpr int X_SZ = N_SZ > H_SZ ? N_SZ : H_SZ;
-  static constexpr int NORM_SZ = 4 * NG, VN_SZ = 16 * NG;
-  static constexpr int WAVE_SZ = (U_SZ + F_SZ + X_SZ + NORM_SZ + VN_SZ + 64 + 48 + 3) / 4 * 4;
-  // global fragment offsets (doubles), in the order the host packs them
-  static constexpr int FI = NQT * KS * 64, FW = NT * KQ * 64, FL = NT * KG * 64;
-  static constexpr int OFF_IQ = 0, OFF_DRQ = FI, OFF_DSQ = 2 * FI, OFF_WR = 3 * FI,
-                       OFF_WS = 3 * FI + FW, OFF_LQ = 3 * FI + 2 * FW, OFF_LRQ = OFF_LQ + FL,
-                       OFF_LSQ = OFF_LQ + 2 * FL, OFF_DRSF = OFF_LQ + 3 * FL,
-                       OFF_IF1 = OFF_DRSF + 2 * NG * Np, TOTAL = OFF_IF1 + q * Nfp;
-  static constexpr int LDS_TAB = 2 * NG * Np + q * Nfp;  // face-point tables in LDS
-};
-
-template <int N>
 __device__ __forceinline__ void oi_tiles(const DeviceTables& t, const KernelPhysics& ph,
                                          const double* __restrict__ Uin, double* __restrict__ Uout,
                                          double* __restrict__ K1, double a, double b, double dt,
@@ -1255,8 +1230,9 @@ oi_stage_kernel(DeviceTables t, KernelPhysics ph, const double* __restrict__ Uin
   __shared__ __attribute__((aligned(16))) double sTab[P::LDS_TAB];
   __shared__ __attribute__((aligned(16))) double sWave[W * P::WAVE_SZ];
   __shared__ int sConnW[W * 12];
-  for (int i = threadIdx.x; i < P::LDS_TAB; i += 64 * W) sTab[i] = t.oi[P::OFF_DRSF + i];
-  for (int i = threadIdx.x; i < W * P::WAVE_SZ; i += 64 * W) sWave[i] = 0.0;
+  // only the state rows' pads are read unwritten
+  copy_values_to_lds<P::LDS_TAB, W>(t.oi + P::OFF_DRSF, sTab);
+  for (int i = threadIdx.x; i < W * P::U_SZ; i += 64 * W) sWave[i / P::U_SZ * P::WAVE_SZ + i % P::U_SZ] = 0.0;
   __syncthreads();
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: tile indices stay scalar
   const int64_t ntiles = (t.K + P::EPT - 1) / P::EPT;

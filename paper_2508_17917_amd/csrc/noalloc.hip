@@ -114,9 +114,9 @@ extern "C" int dg_rk_steps_noalloc(dg_ctx* c, double* U, double* K1, int nsteps,
   if (!std::isfinite(dt)) return dgmi::ctx_fail(c, DG_EINVAL, "dt is not finite");
   const size_t state_doubles = (size_t)c->K * 4 * c->ref.Np;
   const Carve cv = carve(c->noalloc_scratch, state_doubles, c->force_blocks,
-                         c->overint || !dgmi::traces_pay(c->N, c->precision, c->K, nsteps)
-                             ? 0
-                             : dgmi::ctx_trace_bytes(c));
+                         dgmi::traces_pay(c->N, dgmi::ctx_form(c), c->K, nsteps)
+                             ? dgmi::ctx_trace_bytes(c)
+                             : 0);
   if (cv.doubles > kScratchDoubles)
     return dgmi::ctx_fail(c, DG_EINVAL,
                           "state of " + std::to_string(state_doubles * sizeof(double)) +

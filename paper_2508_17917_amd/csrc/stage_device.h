@@ -122,6 +122,13 @@ __device__ __forceinline__ void copy_to_lds(const T* __restrict__ src, T* dst) {
   }
 }
 
+// The same for any count of doubles (the last one by itself where it is odd).
+template <int N, int W>
+__device__ __forceinline__ void copy_values_to_lds(const double* __restrict__ src, double* dst) {
+  copy_to_lds<N / 2 * 2, W>(src, dst);
+  if (N % 2 != 0 && threadIdx.x == 0) dst[N - 1] = src[N - 1];
+}
+
 // Node index of face node j (counter-clockwise) on face f; rows of the node
 // numbering start at i(N+1) - i(i-1)/2.
 template <int N>
@@ -442,6 +449,33 @@ __device__ __forceinline__ void force_wave(const DeviceTables& t, const KernelPh
     if (lane == 0) atomicExch(t.force_ticket, 0u);
   }
 }
+
+// Sizes of the over-integrated stage of order N and the layout of its operator
+// fragments and face-point tables (the order the host packs them in).
+template <int N>
+struct OIOrder {
+  using O = Order<N, double>;
+  static constexpr int Np = O::Np, Nfp = O::Nfp, S = O::S, NT = O::NT, KS = O::KS, RS = O::RS;
+  static constexpr int q = oi_points(N), Nq = q * q, NG = 3 * q;
+  static constexpr int NQT = (Nq + 15) / 16;   // 16-point chunks of the element rule
+  static constexpr int KQ = (Nq + 3) / 4;      // k-steps over the element points
+  static constexpr int KG = (NG + 3) / 4;      // k-steps over the face points
+  static constexpr int EPT = (64 / NG) < 4 ? ((64 / NG) > 0 ? 64 / NG : 1) : 4;
+  static constexpr int FRS = 17;               // padded LDS row of one flux chunk
+  static constexpr int GRS = 4 * KG + 1;       // padded LDS row of the face terms
+  static constexpr int U_SZ = 16 * RS, F_SZ = 32 * FRS;
+  static constexpr int N_SZ = 12 * S, H_SZ = 48 * GRS;
+  static constexpr int X_SZ = N_SZ > H_SZ ? N_SZ : H_SZ;
+  static constexpr int NORM_SZ = 4 * NG, VN_SZ = 16 * NG;
+  static constexpr int WAVE_SZ = (U_SZ + F_SZ + X_SZ + NORM_SZ + VN_SZ + 64 + 48 + 3) / 4 * 4;
+  // global fragment offsets (doubles), in the order the host packs them
+  static constexpr int FI = NQT * KS * 64, FW = NT * KQ * 64, FL = NT * KG * 64;
+  static constexpr int OFF_IQ = 0, OFF_DRQ = FI, OFF_DSQ = 2 * FI, OFF_WR = 3 * FI,
+                       OFF_WS = 3 * FI + FW, OFF_LQ = 3 * FI + 2 * FW, OFF_LRQ = OFF_LQ + FL,
+                       OFF_LSQ = OFF_LQ + 2 * FL, OFF_DRSF = OFF_LQ + 3 * FL,
+                       OFF_IF1 = OFF_DRSF + 2 * NG * Np, TOTAL = OFF_IF1 + q * Nfp;
+  static constexpr int LDS_TAB = 2 * NG * Np + q * Nfp;  // face-point tables in LDS
+};
 
 // workgroups of W waves for the wall force in a stage launch: one wave per 64
 // wall face nodes (the partials of the launch's input state), then the wave

@@ -125,6 +125,7 @@ int launch_face_traces_n(int form, const DeviceTables& t, const KernelPhysics& p
 }  // namespace
 
 size_t trace_bytes(int N, int form, int64_t K) {
+  if (form == kFormOverint) return (size_t)K * 3 * oi_points(N) * 8 * sizeof(double);
   if (form < 0 || form > 2) return 0;
   return (size_t)K * 3 * (N + 1) * 4 * (form == 2 ? sizeof(float) : sizeof(double));
 }
@@ -133,6 +134,8 @@ int launch_trace_stage(int N, int form, const StageTuning& tune, const DeviceTab
                        const double* Uin, double* Uout, double* K1, double a, double b, double dt,
                        const void* tr_in, void* tr_out, void* stream, std::string& err) {
   hipStream_t s = (hipStream_t)stream;
+  if (form == kFormOverint)
+    return launch_oi_trace_stage(N, tune, t, ph, Uin, Uout, K1, a, b, dt, tr_in, tr_out, stream, err);
   switch (N) {
     case 1: return launch_trace_stage_n<1>(form, tune, t, ph, Uin, Uout, K1, a, b, dt, tr_in, tr_out, s, err);
     case 2: return launch_trace_stage_n<2>(form, tune, t, ph, Uin, Uout, K1, a, b, dt, tr_in, tr_out, s, err);
@@ -147,6 +150,7 @@ int launch_trace_stage(int N, int form, const StageTuning& tune, const DeviceTab
 int launch_face_traces(int N, int form, const DeviceTables& t, const KernelPhysics& ph, const double* U, void* tr,
                        void* stream, std::string& err) {
   hipStream_t s = (hipStream_t)stream;
+  if (form == kFormOverint) return launch_oi_face_traces(N, t, ph, U, tr, stream, err);
   switch (N) {
     case 1: return launch_face_traces_n<1>(form, t, ph, U, tr, s, err);
     case 2: return launch_face_traces_n<2>(form, t, ph, U, tr, s, err);

@@ -40,7 +40,9 @@ def _torch():
 def _solver(mesh, p, precision, theta):
     from paper_2508_17917_amd import Solver
     w = mg.physics_params(Re=100.0, M=0.2)
-    return Solver(p, mesh, precision=precision, penalty_mode=0, C_pen=1.0, theta=theta, **w)
+    oi = precision == "overint"
+    return Solver(p, mesh, precision=0 if oi else precision, overintegration=oi, penalty_mode=0, C_pen=1.0,
+                  theta=theta, **w)
 
 
 def _state(torch, s, seed):
@@ -59,13 +61,13 @@ def _chain(torch, s, U, nsteps, dt, vw):
     return Ua, K1, np.array(F)
 
 
-@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("precision", [0, 1, 2, "overint"])
 @pytest.mark.parametrize("p", range(1, 7))
 @pytest.mark.parametrize("name", sorted(MESHES))
 def test_steps_equal_the_stage_chain(name, p, precision):
     torch = _torch()
     theta, vw = {"ogrid": (1.0, (0.01, -0.03)), "periodic": (0.0, (0.02, 0.01)), "two": (-1.0, (0.0, 0.0))}[name]
-    print("[gpu-case] traces %s p=%d precision=%d" % (name, p, precision), flush=True)
+    print("[gpu-case] traces %s p=%d precision=%s" % (name, p, precision), flush=True)
     s = _solver(MESHES[name](), p, precision, theta)
     U = _state(torch, s, p)
     nsteps, dt = 3, 1e-5
