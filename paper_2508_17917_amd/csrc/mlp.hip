@@ -35,9 +35,10 @@ __device__ __forceinline__ void gelu_pair(float z, float& g, float& gp) {
   const float x = fabsf(z) * 0.70710678118654752f;
   const float e = __expf(-x * x);                 // exp(-z^2/2)
   const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * x);
-  const float poly =
-      t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
-  const float half_erfc = 0.5f * poly * e;        // Phi(-|z|)
+  const float half_poly =  // the coefficients halved: exact
+      t * (0.5f * 0.254829592f +
+           t * (0.5f * -0.284496736f + t * (0.5f * 1.421413741f + t * (0.5f * -1.453152027f + t * (0.5f * 1.061405429f)))));
+  const float half_erfc = half_poly * e;          // Phi(-|z|)
   const float Phi = z >= 0.f ? 1.0f - half_erfc : half_erfc;
   g = z * Phi;
   gp = Phi + z * e * 0.39894228040143268f;        // 1/sqrt(2 pi)
@@ -351,21 +352,19 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs g) {
 // ---------------------------------------------------------------- fused training step
 // One training step's forward pass, loss, backward pass and weight gradients
 // in one launch, for the shapes in_pad = 16 KIT, H = 16 HT, out_pad = 16 OT.
-// A workgroup of four waves takes 64 samples at a time, one 16-row tile per
-// wave.  A wave's tile goes through the three layers in registers: the
-// transposed products (weights as the row operand) leave lane l with sample
-// l%16 and four consecutive output columns, which are exactly its B operand
-// for the next layer, and the GELU derivatives stay in FP32 registers for the
-// backward pass.  What the weight gradients need -- the normalised inputs,
-// both hidden activations and the three output gradients -- is written to LDS
-// transposed ([column][sample], bfloat16), so that after a barrier every
-// wave reads its operands as 8-byte words: wave w accumulates the output
-// tiles of dW1, dW2 with row tiles w and w + 4, and of dW3 with row tile w,
-// over the block's 64 samples on the matrix cores.  The bias gradients are
-// per-thread sums over the same arrays (fixed order).  At the end each
-// workgroup writes its whole gradient (the parameter vector's layout) as one
-// partial; reduce_parts_kernel sums them in a fixed order.  HBM traffic per
-// sample: the inputs and targets only.
+// A workgroup of eight (or four) waves takes 16 samples per wave at a time.  A
+// wave's tile goes through the three layers in registers: the transposed
+// products (weights as the row operand) leave lane l with sample l%16 and four
+// consecutive output columns, which are exactly its B operand for the next
+// layer, and the GELU derivatives stay in FP32 registers for the backward pass.
+// What the weight gradients need -- the normalised inputs, both hidden
+// activations and the three output gradients -- is written to LDS (bfloat16),
+// and after a barrier every wave accumulates its output tiles of dW1, dW2 and
+// dW3 over the block's samples on the matrix cores.  The bias gradients are
+// per-lane sums over the same arrays (fixed order).  At the end each workgroup
+// writes its whole gradient (the parameter vector's layout) as one partial;
+// reduce_parts_kernel sums them in a fixed order.  HBM traffic per sample: the
+// inputs and targets only.
 struct TrainArgs {
   const float* X;
   int64_t ldx;
@@ -392,7 +391,8 @@ struct TrainArgs {
 };
 
 __device__ __forceinline__ bf16x4 bf4(const float v[4]) {
-  return bf16x4{(short)f2bf(v[0]), (short)f2bf(v[1]), (short)f2bf(v[2]), (short)f2bf(v[3])};
+  typedef __bf16 nat4 __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(bf16x4, nat4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]});
 }
 __device__ __forceinline__ bf16x4 ld_bf4(const unsigned short* p) {
   const uint2 w = *(const uint2*)p;
@@ -405,7 +405,6 @@ __device__ __forceinline__ bf16x4 ld_bf4(const unsigned short* p) {
 // k values to (group, slot) that both operands share gives the product.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x4 mma32(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
@@ -413,291 +412,387 @@ __device__ __forceinline__ f32x4 mma32(bf16x8 a, bf16x8 b, f32x4 c) {
 __device__ __forceinline__ bf16x8 cat8(bf16x4 lo, bf16x4 hi) {
   return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
-// eight consecutive bfloat16 values (16-byte aligned)
-__device__ __forceinline__ bf16x8 ld_bf8(const unsigned short* p) {
-  return __builtin_bit_cast(bf16x8, *(const u32x4*)p);
+// Four 16-bit values of a column of an LDS array, one from each of four rows:
+// lane i of a group of 16 passes the address of row i / 4 (of its group's four),
+// columns 4 (i % 4) .. + 3 of the 16, and receives column i.
+__device__ __forceinline__ bf16x4 ld_tr4(const unsigned short* p) {
+  typedef __attribute__((address_space(3))) bf16x4* lds_p;
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)p);
 }
 
-template <int KIT, int HT, int OT>
+// Shapes of the training kernel: KIT, HT and OT 16-column tiles of inputs,
+// hidden units and outputs, NW waves of one 16-sample tile each (a block of the
+// batch is 16 NW samples).  Everything lies in LDS as [row][column] with rows
+// padded by 16 values: rows eight banks apart, so that the row-wise and the
+// transposing 8-byte reads of a wave meet each bank twice, the least they can.
+template <int KIT, int HT, int OT, int NW>
 struct TrainShape {
-  static constexpr int KI = 16 * KIT, H = 16 * HT, NO = 16 * OT;
-  static constexpr int L1 = KI + 4, L2 = H + 4, L3 = H + 4;  // weight rows in LDS
-  static constexpr int LT = 64 + 8;  // transposed rows (samples; 16-byte aligned, no bank aliasing)
-  static constexpr int W_SZ = H * L1 + H * L2 + NO * L3;
-  static constexpr int T_SZ = LT * (KI + 4 * H + NO);
+  static constexpr int KI = 16 * KIT, H = 16 * HT, NO = 16 * OT, SB = 16 * NW;
+  static constexpr int LI = KI + 16, LH = H + 16, LO = NO + 16;
+  static constexpr int W_SZ = H * LI + H * LH + NO * LH;
+  static constexpr int A_SZ = SB * (LI + 2 * LH + LO);  // X | H1 | H2 | dY
+  static constexpr int C_SZ = 2 * KI + 2 * H + 3 * NO;  // normalisation and biases (floats)
 };
 
-template <int KIT, int HT, int OT>
-__global__ __launch_bounds__(256) void train_kernel(TrainArgs g) {
-  using S = TrainShape<KIT, HT, OT>;
-  constexpr int KI = S::KI, H = S::H, NO = S::NO, L1 = S::L1, L2 = S::L2, L3 = S::L3, LT = S::LT;
-  static_assert(HT == 8 && OT <= 4, "shape not built: waves take row tiles wid and wid + 4");
-  static_assert(KIT % 2 == 0 && OT % 2 == 0, "the double-depth products pair k-tiles");
+// One training step's gradient: forward, loss, backward and weight gradients of
+// a workgroup's samples, a block of 16 NW at a time, 16 a wave.  The products of
+// the layers are formed transposed (the weights as the row operand), so a lane
+// ends with four consecutive columns of one sample, its operand of the next
+// layer; those go to LDS by sample as 8-byte words.  The weight gradients need
+// them by column and the backward products the weights by column: both come
+// through the transposing LDS read, two instructions per operand.  The gradient
+// at a hidden layer takes its activation's place once that has served (dZ2 that
+// of H2, dZ1 that of dZ2).
+//
+// Two waves per SIMD (the LDS holds one workgroup, 158 of 160 KB) cover each
+// other's LDS and matrix latencies.  65,536 samples, 28 -> 128 -> 128 -> 24:
+// 42 us.  With four waves of two tiles each, every lane's instructions in one
+// chain, 60 us; with transposed copies written value by value, the transposed
+// weights gathered by eight 2-byte reads an operand and the bias sums left to
+// one wave, 66 us.  Bound by vector issue: 64 GELU pairs a lane and block, each
+// of 21 instructions, two of them quarter-rate, are 60 % of it; the
+// matrix products are 4.4 of about 27 thousand cycles a block and SIMD.
+template <int KIT, int HT, int OT, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void train_kernel(
+    TrainArgs g) {
+  using S = TrainShape<KIT, HT, OT, NW>;
+  constexpr int KI = S::KI, H = S::H, NO = S::NO, LI = S::LI, LH = S::LH, LO = S::LO;
+  constexpr int NT = 64 * NW, RT = HT / NW, CT = OT * HT / NW;  // threads; row tiles of dW1, dW2, column tiles of dW3 a wave
+  static_assert(HT == 8 && (OT == 2 || OT == 4) && (NW == 4 || NW == 8) && NW * OT <= 16, "shape not built");
+  static_assert(KIT % 2 == 0, "the double-depth products pair k-tiles");
   __shared__ __attribute__((aligned(16))) unsigned short sW[S::W_SZ];
-  __shared__ __attribute__((aligned(16))) unsigned short sT[S::T_SZ];
-  __shared__ double sLoss[4];
-  unsigned short* sW1 = sW;
-  unsigned short* sW2 = sW1 + H * L1;
-  unsigned short* sW3 = sW2 + H * L2;
-  unsigned short* tX = sT;                 // [KI][LT]
-  unsigned short* tH1 = tX + KI * LT;      // [H][LT]
-  unsigned short* tH2 = tH1 + H * LT;
-  unsigned short* tZ1 = tH2 + H * LT;      // dZ1
-  unsigned short* tZ2 = tZ1 + H * LT;      // dZ2
-  unsigned short* tDY = tZ2 + H * LT;      // [NO][LT]
+  __shared__ __attribute__((aligned(16))) unsigned short sA[S::A_SZ];
+  __shared__ __attribute__((aligned(16))) float sC[S::C_SZ];
+  __shared__ double sLoss[NW];
+  unsigned short* sW1 = sW;             // [H][LI]
+  unsigned short* sW2 = sW1 + H * LI;   // [H][LH]
+  unsigned short* sW3 = sW2 + H * LH;   // [NO][LH]
+  unsigned short* sX = sA;              // [SB][LI]
+  unsigned short* sH1 = sX + S::SB * LI;
+  unsigned short* sH2 = sH1 + S::SB * LH;
+  unsigned short* sDY = sH2 + S::SB * LH;
+  unsigned short* sZ = sH2;             // dZ2, then dZ1
+  float* sMean = sC;
+  float* sRstd = sMean + KI;
+  float* sB1 = sRstd + KI;
+  float* sB2 = sB1 + H;
+  float* sB3 = sB2 + H;
+  float* sOm = sB3 + NO;
+  float* sOs = sOm + NO;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int ar = lane & 15, ak = 4 * (lane >> 4);
-
-  // weights into LDS, 8-byte words
-  for (int i = threadIdx.x; i < H * (KI / 4); i += 256) {
-    const int n = i / (KI / 4), k = 4 * (i - n * (KI / 4));
-    *(uint2*)(sW1 + n * L1 + k) = *(const uint2*)(g.W1 + (int64_t)n * g.ldw1 + k);
-  }
-  for (int i = threadIdx.x; i < H * (H / 4); i += 256) {
-    const int n = i / (H / 4), k = 4 * (i - n * (H / 4));
-    *(uint2*)(sW2 + n * L2 + k) = *(const uint2*)(g.W2 + (int64_t)n * g.ldw2 + k);
-  }
-  for (int i = threadIdx.x; i < NO * (H / 4); i += 256) {
-    const int n = i / (H / 4), k = 4 * (i - n * (H / 4));
-    *(uint2*)(sW3 + n * L3 + k) = *(const uint2*)(g.W3 + (int64_t)n * g.ldw3 + k);
-  }
-
-  f32x4 acc1[2][KIT], acc2[2][HT], acc3[HT];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-#pragma unroll
-    for (int t = 0; t < KIT; ++t) acc1[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t = 0; t < HT; ++t) acc2[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-#pragma unroll
-  for (int t = 0; t < HT; ++t) acc3[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float bsum[2] = {0.f, 0.f};  // bias entries threadIdx.x and threadIdx.x + 256
-  double loss = 0.0;
+  const int tr = ak + (ar >> 2), tc = 4 * (ar & 3);  // row and first column of a transposing read
 
   const int64_t s_begin = (int64_t)blockIdx.x * g.chunk;
   const int64_t s_end = s_begin + g.chunk < g.B ? s_begin + g.chunk : g.B;
-  // a tile's inputs and targets (raw FP32), loaded one block ahead
-  float xr[KIT][4], tr[OT][4];
+  // the samples' inputs and targets (raw FP32), loaded one block ahead; past the
+  // end or beyond n_in, n_out a valid element that is not used
+  float xr[KIT][4], tv[OT][4];
+  typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+  const bool quads = g.n_in % 4 == 0 && g.n_out % 4 == 0;
   auto load = [&](int64_t s0) {
-    const int64_t row = s0 + 16 * wid + ar;
-    const bool rok = row < s_end;
+    int k0 = ak;
+    asm("" : "+v"(k0));  // the columns' limits are formed anew, not held over the blocks
+    int64_t row = s0 + 16 * wid + ar;
+    row = row < s_end ? row : s_end - 1;
+    const float* x = g.X + row * g.ldx;
+    const float* t = g.T + row * g.ldt;
+    if (quads) {
 #pragma unroll
-    for (int ks = 0; ks < KIT; ++ks)
+      for (int i = 0; i < KIT; ++i) {
+        const int k = 16 * i + k0;
+        const f4u v = *(const f4u*)(x + (k < g.n_in ? k : 0));
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int k = 16 * ks + ak + j;
-        xr[ks][j] = (rok && k < g.n_in) ? g.X[row * g.ldx + k] : 0.f;
+        for (int j = 0; j < 4; ++j) xr[i][j] = v[j];
       }
 #pragma unroll
-    for (int t = 0; t < OT; ++t)
+      for (int i = 0; i < OT; ++i) {
+        const int c = 16 * i + k0;
+        const f4u v = *(const f4u*)(t + (c < g.n_out ? c : 0));
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int c = 16 * t + ak + v;
-        tr[t][v] = (rok && c < g.n_out) ? g.T[row * g.ldt + c] : 0.f;
+        for (int j = 0; j < 4; ++j) tv[i][j] = v[j];
       }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4 * KIT; ++i) {
+        const int k = 16 * (i / 4) + k0 + i % 4;
+        xr[i / 4][i % 4] = x[k < g.n_in ? k : 0];
+      }
+#pragma unroll
+      for (int i = 0; i < 4 * OT; ++i) {
+        const int c = 16 * (i / 4) + k0 + i % 4;
+        tv[i / 4][i % 4] = t[c < g.n_out ? c : 0];
+      }
+    }
   };
   if (s_begin < s_end) load(s_begin);
+
+  // weights (16-byte vectors, every load in flight), biases, normalisation
+  {
+    constexpr int N1 = H * KI / 8, N2 = H * H / 8, N3 = NO * H / 8, NV = (N1 + N2 + N3) / NT;
+    static_assert((N1 + N2 + N3) % NT == 0, "whole rounds of the workgroup");
+    static_assert(N1 % NT == 0 && N2 % NT == 0, "a round stays in one matrix");
+    uint4 w[NV];
+#pragma unroll
+    for (int r = 0; r < NV; ++r) {
+      const int i = threadIdx.x + NT * r;
+      const unsigned short* src;
+      if (NT * r < N1)
+        src = g.W1 + (int64_t)(i / (KI / 8)) * g.ldw1 + 8 * (i % (KI / 8));
+      else if (NT * r < N1 + N2)
+        src = g.W2 + (int64_t)((i - N1) / (H / 8)) * g.ldw2 + 8 * (i % (H / 8));
+      else
+        src = g.W3 + (int64_t)((i - N1 - N2) / (H / 8)) * g.ldw3 + 8 * (i % (H / 8));
+      w[r] = *(const uint4*)src;
+    }
+    for (int i = threadIdx.x; i < H; i += NT) {
+      sB1[i] = g.b1[i];
+      sB2[i] = g.b2[i];
+      if (i < KI) {
+        sMean[i] = i < g.n_in ? g.in_mean[i] : 0.f;
+        sRstd[i] = i < g.n_in ? g.in_rstd[i] : 0.f;
+      }
+      if (i < NO) {
+        sB3[i] = i < g.n_out ? g.b3[i] : 0.f;
+        sOm[i] = i < g.n_out ? g.out_mean[i] : 0.f;
+        sOs[i] = i < g.n_out ? g.out_std[i] : 1.f;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < NV; ++r) {
+      const int i = threadIdx.x + NT * r;
+      unsigned short* dst;
+      if (NT * r < N1)
+        dst = sW1 + i / (KI / 8) * LI + 8 * (i % (KI / 8));
+      else if (NT * r < N1 + N2)
+        dst = sW2 + (i - N1) / (H / 8) * LH + 8 * (i % (H / 8));
+      else
+        dst = sW3 + (i - N1 - N2) / (H / 8) * LH + 8 * (i % (H / 8));
+      *(uint4*)dst = w[r];
+    }
+  }
+
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 acc1[RT][KIT], acc2[RT][HT], acc3[CT];
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+#pragma unroll
+    for (int t = 0; t < KIT; ++t) acc1[i][t] = zero;
+#pragma unroll
+    for (int t = 0; t < HT; ++t) acc2[i][t] = zero;
+  }
+#pragma unroll
+  for (int t = 0; t < CT; ++t) acc3[t] = zero;
+  // bias sums of one column: of dZ1 and dZ2 by four waves each (the same four if
+  // there are no more), of dY by one; the lanes above 32 sum the second 64 samples
+  float bsz = 0.f, bs1 = 0.f, bsy = 0.f;
+  double loss = 0.0;
   __syncthreads();
 
+  // the operand of a weight-gradient product: columns 16 t .. + 15 of a [sample]
+  // [column] array, its samples 32 ks + 8 (lane / 16) .. + 7 as the k-slots
+  auto by_col = [&](const unsigned short* arr, int ld, int t, int ks) {
+    const unsigned short* p = arr + (32 * ks + 2 * ak + (ar >> 2)) * ld + 16 * t + tc;
+    return cat8(ld_tr4(p), ld_tr4(p + 4 * ld));
+  };
+  // a weight as the row operand of a backward product: rows 32 q + ak + j and
+  // 32 q + 16 + ak + j as the k-slots, columns 16 t .. + 15
+  auto w_col = [&](const unsigned short* w, int q, int t) {
+    const unsigned short* p = w + (32 * q + tr) * LH + 16 * t + tc;
+    return cat8(ld_tr4(p), ld_tr4(p + 16 * LH));
+  };
+  // a lane's four columns of tile t of its sample, into the sample's row
+  auto put = [&](unsigned short* arr, int ld, int t, bf16x4 v) {
+    *(bf16x4*)(arr + (16 * wid + ar) * ld + 16 * t + ak) = v;
+  };
+  // sum over 64 samples from sample s of a lane's column (tile t, column ar), in fours
+  auto col_sum = [&](const unsigned short* arr, int ld, int t, int s) {
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const bf16x4 v = ld_tr4(arr + (s + 4 * i + (ar >> 2)) * ld + 16 * t + tc);
+      float q[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) q[j] = __uint_as_float((unsigned)(unsigned short)v[j] << 16);
+      sum += ((q[0] + q[1]) + q[2]) + q[3];
+    }
+    return sum;
+  };
+  // column sums of an array of HT tiles by waves w0 .. w0 + 3: two tiles each
+  auto sums_h = [&](const unsigned short* arr, int w0, float& bs) {
+    if (wid < w0 || wid >= w0 + 4) return;
+    const int hi = lane >> 5;
+    const float v = col_sum(arr, LH, 2 * (wid - w0) + ((lane >> 4) & 1), NW == 8 ? 64 * hi : 0);
+    bs += v;
+    if (NW == 8) bs += __shfl_down(v, 32, 64);
+  };
+
 #pragma unroll 1
-  for (int64_t s0 = s_begin; s0 < s_end; s0 += 64) {
-    const int64_t row = s0 + 16 * wid + ar;
-    const bool rok = row < s_end;
-    const int col = 16 * wid + ar;  // this lane's sample column in the transposed arrays
+  for (int64_t s0 = s_begin; s0 < s_end; s0 += S::SB) {
+    const bool rok = s0 + 16 * wid + ar < s_end;
     // ---- forward: normalised inputs (zero beyond n_in and past the end)
     bf16x4 a1[KIT];
 #pragma unroll
     for (int ks = 0; ks < KIT; ++ks) {
+      const f32x4 mean = *(const f32x4*)(sMean + 16 * ks + ak), rstd = *(const f32x4*)(sRstd + 16 * ks + ak);
       float v[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int k = 16 * ks + ak + j;
-        v[j] = (rok && k < g.n_in) ? (xr[ks][j] - g.in_mean[k]) * g.in_rstd[k] : 0.f;
-      }
+      for (int j = 0; j < 4; ++j)
+        v[j] = (rok && 16 * ks + ak + j < g.n_in) ? (xr[ks][j] - mean[j]) * rstd[j] : 0.f;
       a1[ks] = bf4(v);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) tX[(16 * ks + ak + j) * LT + col] = (unsigned short)a1[ks][j];
+      put(sX, LI, ks, a1[ks]);
     }
-    float d1[HT][4], d2[HT][4];  // GELU derivatives at the pre-activations
-    bf16x4 h1[HT], h2[HT];
-    // the HT output tiles as independent accumulator chains (k-steps outer)
-    f32x4 acc[HT];
-#pragma unroll
-    for (int t = 0; t < HT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     // the double-depth products take k-tiles 2q (slots 0-3) and 2q + 1 (slots
     // 4-7): lane group g holds k = 16 (2q) + 4g + j and 16 (2q + 1) + 4g + j,
     // exactly the values the previous product left in the lane
-#pragma unroll
-    for (int q = 0; q < KIT / 2; ++q) {
-      const bf16x8 b = cat8(a1[2 * q], a1[2 * q + 1]);
-#pragma unroll
-      for (int t = 0; t < HT; ++t) {
-        const unsigned short* w = sW1 + (16 * t + ar) * L1 + 32 * q + ak;
-        acc[t] = mma32(cat8(ld_bf4(w), ld_bf4(w + 16)), b, acc[t]);
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < HT; ++t) {
+    float d1[HT][4], d2[HT][4];  // GELU derivatives at the pre-activations
+    bf16x4 h1[HT], h2[HT];
+    f32x4 acc[HT];
+    auto w_row = [&](const unsigned short* w, int ld, int q, int t) {
+      const unsigned short* p = w + (16 * t + ar) * ld + 32 * q + ak;
+      return cat8(ld_bf4(p), ld_bf4(p + 16));
+    };
+    // GELU and its derivative, the latter formed here: left to its use, three
+    // values would wait for it
+    auto gelu = [&](const f32x4& z, const float* bias, float d[4]) {
+      const f32x4 bv = *(const f32x4*)bias;
       float v[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) gelu_pair(acc[t][j] + g.b1[16 * t + ak + j], v[j], d1[t][j]);
-      h1[t] = bf4(v);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) tH1[(16 * t + ak + j) * LT + col] = (unsigned short)h1[t][j];
-    }
-#pragma unroll
-    for (int t = 0; t < HT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < HT / 2; ++q) {
-      const bf16x8 b = cat8(h1[2 * q], h1[2 * q + 1]);
-#pragma unroll
-      for (int t = 0; t < HT; ++t) {
-        const unsigned short* w = sW2 + (16 * t + ar) * L2 + 32 * q + ak;
-        acc[t] = mma32(cat8(ld_bf4(w), ld_bf4(w + 16)), b, acc[t]);
+      for (int j = 0; j < 4; ++j) {
+        gelu_pair(z[j] + bv[j], v[j], d[j]);
+        asm("" : "+v"(d[j]));
       }
-    }
+      return bf4(v);
+    };
+#pragma unroll
+    for (int t = 0; t < HT; ++t) acc[t] = zero;
+#pragma unroll
+    for (int q = 0; q < KIT / 2; ++q)
+#pragma unroll
+      for (int t = 0; t < HT; ++t) acc[t] = mma32(w_row(sW1, LI, q, t), cat8(a1[2 * q], a1[2 * q + 1]), acc[t]);
 #pragma unroll
     for (int t = 0; t < HT; ++t) {
-      float v[4];
+      h1[t] = gelu(acc[t], sB1 + 16 * t + ak, d1[t]);
+      put(sH1, LH, t, h1[t]);
+      acc[t] = zero;
+    }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) gelu_pair(acc[t][j] + g.b2[16 * t + ak + j], v[j], d2[t][j]);
-      h2[t] = bf4(v);
+    for (int q = 0; q < HT / 2; ++q)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) tH2[(16 * t + ak + j) * LT + col] = (unsigned short)h2[t][j];
+      for (int t = 0; t < HT; ++t) acc[t] = mma32(w_row(sW2, LH, q, t), cat8(h1[2 * q], h1[2 * q + 1]), acc[t]);
+#pragma unroll
+    for (int t = 0; t < HT; ++t) {
+      h2[t] = gelu(acc[t], sB2 + 16 * t + ak, d2[t]);
+      put(sH2, LH, t, h2[t]);
+      acc[t] = zero;
     }
     // ---- output layer and loss: dY = 2 (y - t_n) / (B n_out), normalised units
     bf16x4 dy[OT];
 #pragma unroll
-    for (int t = 0; t < OT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < HT / 2; ++q)
 #pragma unroll
-    for (int q = 0; q < HT / 2; ++q) {
-      const bf16x8 b = cat8(h2[2 * q], h2[2 * q + 1]);
-#pragma unroll
-      for (int t = 0; t < OT; ++t) {
-        const unsigned short* w = sW3 + (16 * t + ar) * L3 + 32 * q + ak;
-        acc[t] = mma32(cat8(ld_bf4(w), ld_bf4(w + 16)), b, acc[t]);
-      }
-    }
+      for (int t = 0; t < OT; ++t) acc[t] = mma32(w_row(sW3, LH, q, t), cat8(h2[2 * q], h2[2 * q + 1]), acc[t]);
 #pragma unroll
     for (int t = 0; t < OT; ++t) {
+      const f32x4 b3 = *(const f32x4*)(sB3 + 16 * t + ak), om = *(const f32x4*)(sOm + 16 * t + ak),
+                  os = *(const f32x4*)(sOs + 16 * t + ak);
       float v[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int c = 16 * t + ak + j;
-        v[j] = 0.f;
-        if (rok && c < g.n_out) {
-          const float tn = (tr[t][j] - g.out_mean[c]) / g.out_std[c];
-          const float res = acc[t][j] + g.b3[c] - tn;
-          loss += (double)res * (double)res;
-          v[j] = g.loss_scale * res;
-        }
+        const bool ok = rok && 16 * t + ak + j < g.n_out;
+        const float tn = (tv[t][j] - om[j]) / os[j];
+        const float res = ok ? acc[t][j] + b3[j] - tn : 0.f;
+        loss += (double)res * (double)res;
+        v[j] = ok ? g.loss_scale * res : 0.f;
       }
       dy[t] = bf4(v);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) tDY[(16 * t + ak + j) * LT + col] = (unsigned short)dy[t][j];
+      put(sDY, LO, t, dy[t]);
     }
     // the next block's inputs, in flight during the backward pass
-    if (s0 + 64 < s_end) load(s0 + 64);
-    // ---- backward: dZ2 = (dY W3) gelu'(Z2), dZ1 = (dZ2 W2) gelu'(Z1); the
-    // transposed weights are read from the row-major copies, four rows apart
-    bf16x4 z2[HT];
+    if (s0 + S::SB < s_end) load(s0 + S::SB);
+    __syncthreads();
+
+    // ---- dW3 += dY^T H2 (wave: row tile wid % OT, CT column tiles) and
+    // dZ2 = (dY W3) gelu'(Z2)
 #pragma unroll
-    for (int t = 0; t < HT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int ks = 0; ks < NW / 2; ++ks) {
+      const bf16x8 ady = by_col(sDY, LO, wid % OT, ks);
 #pragma unroll
-    for (int q = 0; q < OT / 2; ++q) {
-      const bf16x8 b = cat8(dy[2 * q], dy[2 * q + 1]);
+      for (int kt = 0; kt < CT; ++kt) acc3[kt] = mma32(ady, by_col(sH2, LH, wid / OT * CT + kt, ks), acc3[kt]);
+    }
+    // a hidden layer's gradient: product with the weights w above, times gelu'
+    bf16x4 z[HT];
+    auto back = [&](const unsigned short* w, const bf16x4* zin, int nq, const float d[HT][4]) {
+#pragma unroll
+      for (int t = 0; t < HT; ++t) acc[t] = zero;
+#pragma unroll
+      for (int q = 0; q < nq; ++q)
+#pragma unroll
+        for (int t = 0; t < HT; ++t) acc[t] = mma32(w_col(w, q, t), cat8(zin[2 * q], zin[2 * q + 1]), acc[t]);
 #pragma unroll
       for (int t = 0; t < HT; ++t) {
-        const unsigned short* w = sW3 + (32 * q + ak) * L3 + 16 * t + ar;
-        const unsigned short* v = w + 16 * L3;
-        const s16x8 wt{(short)w[0], (short)w[L3], (short)w[2 * L3], (short)w[3 * L3],
-                       (short)v[0], (short)v[L3], (short)v[2 * L3], (short)v[3 * L3]};
-        acc[t] = mma32(__builtin_bit_cast(bf16x8, wt), b, acc[t]);
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = acc[t][j] * d[t][j];
+        z[t] = bf4(v);
       }
-    }
-#pragma unroll
-    for (int t = 0; t < HT; ++t) {
-      float v[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = acc[t][j] * d2[t][j];
-      z2[t] = bf4(v);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) tZ2[(16 * t + ak + j) * LT + col] = (unsigned short)z2[t][j];
-    }
-#pragma unroll
-    for (int t = 0; t < HT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < HT / 2; ++q) {
-      const bf16x8 b = cat8(z2[2 * q], z2[2 * q + 1]);
-#pragma unroll
-      for (int t = 0; t < HT; ++t) {
-        const unsigned short* w = sW2 + (32 * q + ak) * L2 + 16 * t + ar;
-        const unsigned short* v = w + 16 * L2;
-        const s16x8 wt{(short)w[0], (short)w[L2], (short)w[2 * L2], (short)w[3 * L2],
-                       (short)v[0], (short)v[L2], (short)v[2 * L2], (short)v[3 * L2]};
-        acc[t] = mma32(__builtin_bit_cast(bf16x8, wt), b, acc[t]);
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < HT; ++t) {
-      float v[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = acc[t][j] * d1[t][j];
-      const bf16x4 z1 = bf4(v);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) tZ1[(16 * t + ak + j) * LT + col] = (unsigned short)z1[j];
+    };
+    back(sW3, dy, OT / 2, d2);
+    if (wid == 3) {
+      const int t = OT == 2 ? (lane >> 4) & 1 : lane >> 4;
+      const float v = col_sum(sDY, LO, t, NW == 8 ? 64 * (lane >> 5) : 0);
+      bsy += v;
+      if (NW == 8) bsy += __shfl_down(v, 32, 64);
     }
     __syncthreads();
-    // ---- weight gradients of the block: dW[n][k] += sum_s dZ[s][n] A[s][k],
-    // the samples as the double-depth k (lane group g: samples 32 ks + 8g ..
-    // 32 ks + 8g + 7, one 16-byte read per operand)
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int sb = 32 * ks + 2 * ak;  // samples sb .. sb + 7 of the block
+    for (int t = 0; t < HT; ++t) put(sZ, LH, t, z[t]);
+    __syncthreads();
+
+    // ---- dW2 += dZ2^T H1 (wave: row tiles wid, wid + NW) and dZ1 = (dZ2 W2) gelu'(Z1)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int nt = wid + 4 * i;
-        const bf16x8 az1 = ld_bf8(tZ1 + (16 * nt + ar) * LT + sb);
-        const bf16x8 az2 = ld_bf8(tZ2 + (16 * nt + ar) * LT + sb);
+    for (int ks = 0; ks < NW / 2; ++ks) {
+      bf16x8 az[RT];
 #pragma unroll
-        for (int kt = 0; kt < KIT; ++kt) acc1[i][kt] = mma32(az1, ld_bf8(tX + (16 * kt + ar) * LT + sb), acc1[i][kt]);
+      for (int i = 0; i < RT; ++i) az[i] = by_col(sZ, LH, wid + NW * i, ks);
 #pragma unroll
-        for (int kt = 0; kt < HT; ++kt) acc2[i][kt] = mma32(az2, ld_bf8(tH1 + (16 * kt + ar) * LT + sb), acc2[i][kt]);
-      }
-      if (wid < OT) {
-        const bf16x8 ady = ld_bf8(tDY + (16 * wid + ar) * LT + sb);
+      for (int kt = 0; kt < HT; ++kt) {
+        const bf16x8 h = by_col(sH1, LH, kt, ks);
 #pragma unroll
-        for (int kt = 0; kt < HT; ++kt) acc3[kt] = mma32(ady, ld_bf8(tH2 + (16 * kt + ar) * LT + sb), acc3[kt]);
+        for (int i = 0; i < RT; ++i) acc2[i][kt] = mma32(az[i], h, acc2[i][kt]);
       }
     }
-    // bias gradients: thread t sums its rows of dZ1 | dZ2 | dY over the block
+    back(sW2, z, HT / 2, d1);
+    sums_h(sZ, NW - 4, bsz);
+    __syncthreads();
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int e = threadIdx.x + 256 * r;
-      if (e < 2 * H + NO) {
-        const unsigned short* rowp = e < H ? tZ1 + e * LT : (e < 2 * H ? tZ2 + (e - H) * LT : tDY + (e - 2 * H) * LT);
-        float sum = 0.f;
+    for (int t = 0; t < HT; ++t) put(sZ, LH, t, z[t]);
+    __syncthreads();
+
+    // ---- dW1 += dZ1^T X
 #pragma unroll
-        for (int s = 0; s < 64; s += 4) {
-          const bf16x4 q = ld_bf4(rowp + s);
-          sum += ((bf2f((unsigned short)q[0]) + bf2f((unsigned short)q[1])) + bf2f((unsigned short)q[2])) +
-                 bf2f((unsigned short)q[3]);
-        }
-        bsum[r] += sum;
+    for (int ks = 0; ks < NW / 2; ++ks) {
+      bf16x8 az[RT];
+#pragma unroll
+      for (int i = 0; i < RT; ++i) az[i] = by_col(sZ, LH, wid + NW * i, ks);
+#pragma unroll
+      for (int kt = 0; kt < KIT; ++kt) {
+        const bf16x8 x = by_col(sX, LI, kt, ks);
+#pragma unroll
+        for (int i = 0; i < RT; ++i) acc1[i][kt] = mma32(az[i], x, acc1[i][kt]);
       }
     }
+    sums_h(sZ, 0, bs1);
     __syncthreads();
   }
 
   // ---- this workgroup's partial: the whole gradient vector
   float* out = g.part + (int64_t)blockIdx.x * g.stride;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int nt = wid + 4 * i;
+  for (int i = 0; i < RT; ++i)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int n = 16 * nt + ak + v;
+      const int n = 16 * (wid + NW * i) + ak + v;
 #pragma unroll
       for (int kt = 0; kt < KIT; ++kt) {
         const int k = 16 * kt + ar;
@@ -706,27 +801,27 @@ __global__ __launch_bounds__(256) void train_kernel(TrainArgs g) {
 #pragma unroll
       for (int kt = 0; kt < HT; ++kt) out[g.woff[1] + (int64_t)n * H + 16 * kt + ar] = acc2[i][kt][v];
     }
-  }
-  if (wid < OT) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int n = 16 * wid + ak + v;
-      if (n < g.n_out)
+  for (int v = 0; v < 4; ++v) {
+    const int n = 16 * (wid % OT) + ak + v;
+    if (n < g.n_out)
 #pragma unroll
-        for (int kt = 0; kt < HT; ++kt) out[g.woff[2] + (int64_t)n * H + 16 * kt + ar] = acc3[kt][v];
-    }
+      for (int kt = 0; kt < CT; ++kt)
+        out[g.woff[2] + (int64_t)n * H + 16 * (wid / OT * CT + kt) + ar] = acc3[kt][v];
   }
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int e = threadIdx.x + 256 * r;
-    if (e < H) out[g.boff[0] + e] = bsum[r];
-    else if (e < 2 * H) out[g.boff[1] + (e - H)] = bsum[r];
-    else if (e < 2 * H + g.n_out) out[g.boff[2] + (e - 2 * H)] = bsum[r];
+  if (lane < 32) {
+    if (wid >= NW - 4) out[g.boff[1] + 32 * (wid - (NW - 4)) + lane] = bsz;
+    if (wid < 4) out[g.boff[0] + 32 * wid + lane] = bs1;
   }
+  if (wid == 3 && lane < NO && lane < g.n_out && (NW == 4 || lane < 32)) out[g.boff[2] + lane] = bsy;
   for (int o = 32; o > 0; o >>= 1) loss += __shfl_down(loss, o, 64);
   if (lane == 0) sLoss[wid] = loss;
   __syncthreads();
-  if (threadIdx.x == 0) g.loss_part[blockIdx.x] = ((sLoss[0] + sLoss[1]) + sLoss[2]) + sLoss[3];
+  if (threadIdx.x == 0) {
+    double sum = sLoss[0];
+    for (int w = 1; w < NW; ++w) sum += sLoss[w];
+    g.loss_part[blockIdx.x] = sum;
+  }
 }
 
 // gradient = sum over the workgroup partials in a fixed order: wave w of a
@@ -1069,9 +1164,9 @@ int mlp_forward(const MlpDev& d, const float* X, int64_t ldx, int64_t B, float* 
 }
 
 namespace {
-template <int KIT, int HT, int OT>
+template <int KIT, int HT, int OT, int NW>
 int train_go(const TrainArgs& a, int blocks, hipStream_t s, std::string& err) {
-  hipLaunchKernelGGL((train_kernel<KIT, HT, OT>), dim3(blocks), dim3(256), 0, s, a);
+  hipLaunchKernelGGL((train_kernel<KIT, HT, OT, NW>), dim3(blocks), dim3(64 * NW), 0, s, a);
   return lerr(err, "training kernel launch");
 }
 
@@ -1106,7 +1201,11 @@ int train_fused(const MlpDev& d, const float* X, int64_t ldx, const float* T, in
     a.woff[l] = d.woff[l];
     a.boff[l] = d.boff[l];
   }
-  int rc = OT == 4 ? train_go<2, 8, 4>(a, blocks, s, err) : train_go<2, 8, 2>(a, blocks, s, err);
+  // eight waves where a workgroup has more than 64 samples and LDS holds 128
+  // samples' activations (up to 32 outputs; wider ones would need 170 KB).  With 64
+  // samples four waves of the eight would run empty tiles.
+  int rc = OT == 4 ? train_go<2, 8, 4, 4>(a, blocks, s, err)
+                   : (chunk > 64 ? train_go<2, 8, 2, 8>(a, blocks, s, err) : train_go<2, 8, 2, 4>(a, blocks, s, err));
   if (rc) return rc;
   if (loss_parts) *loss_parts = blocks;
   hipLaunchKernelGGL(reduce_parts_kernel, dim3((unsigned)((d.nparams + 63) / 64)), dim3(256), 0, s,
