@@ -30,7 +30,6 @@ struct dg_batch {
   int* d_parity = nullptr;
   dgmi::BatchStep* h_steps = nullptr; // pinned staging
   int* h_parity = nullptr;
-  double* d_force = nullptr;
   double* h_force = nullptr;
   dgmi::ForceItem* d_fitems = nullptr;  // wall-force launch descriptors
   dgmi::ForceItem* h_fitems = nullptr;  // pinned staging
@@ -81,7 +80,7 @@ void release(dg_batch* b) {
       if (p) (void)hipFree(p);
   for (void* p : b->tr)
     if (p) (void)hipFree(p);
-  void* dev[] = {b->d_items, b->d_steps, b->d_parity, b->d_force, b->d_fitems};
+  void* dev[] = {b->d_items, b->d_steps, b->d_parity, b->d_fitems};
   for (void* p : dev)
     if (p) (void)hipFree(p);
   if (b->h_steps) (void)hipHostFree(b->h_steps);
@@ -415,7 +414,6 @@ static int batch_build(dg_batch* b, dg_ctx* const* ctxs, int n) {
       (e = hipMemset(b->d_steps, 0, n * sizeof(dgmi::BatchStep))) != hipSuccess ||
       (e = hipMalloc((void**)&b->d_parity, sizeof(int))) != hipSuccess ||
       (e = hipMemset(b->d_parity, 0, sizeof(int))) != hipSuccess ||
-      (e = hipMalloc((void**)&b->d_force, 4 * n * sizeof(double))) != hipSuccess ||
       (e = hipHostMalloc((void**)&b->h_steps, n * sizeof(dgmi::BatchStep))) != hipSuccess ||
       (e = hipHostMalloc((void**)&b->h_parity, sizeof(int))) != hipSuccess ||
       (e = hipHostMalloc((void**)&b->h_force, 4 * n * sizeof(double))) != hipSuccess ||
@@ -531,8 +529,7 @@ int dg_batch_force(dg_batch* b, const double* v_w, double* out, void* stream) {
       const int i = b->inst_of[j];
       dg_ctx* c = b->ctx[i];
       if (c->mesh.wall_faces.empty()) {
-        hipError_t e = hipMemsetAsync(b->d_force + 4 * i, 0, 3 * sizeof(double), s);
-        if (e != hipSuccess) return bhip(b, e, "hipMemsetAsync");
+        for (int k = 0; k < 3; ++k) b->h_force[4 * i + k] = 0.0;
         continue;
       }
       const double vw[2] = {v_w ? v_w[2 * i] : 0.0, v_w ? v_w[2 * i + 1] : 0.0};
@@ -540,7 +537,7 @@ int dg_batch_force(dg_batch* b, const double* v_w, double* out, void* stream) {
       f.t = dgmi::ctx_tables(c);
       f.ph = dgmi::ctx_phys(c, vw);
       f.U = b->parity ? b->B[i] : b->A[i];
-      f.out = b->d_force + 4 * i;
+      f.out = b->h_force + 4 * i;  // pinned: no copy between the launch and the host
       f.block_begin = blocks;
       f.nblocks = c->force_blocks;
       blocks += c->force_blocks;
@@ -557,9 +554,7 @@ int dg_batch_force(dg_batch* b, const double* v_w, double* out, void* stream) {
     int rc = dgmi::launch_batch_force(l.N, b->d_fitems + l.first, l.count, l.blocks, s, err);
     if (rc != 0) return bfail(b, rc, err);
   }
-  hipError_t e = hipMemcpyAsync(b->h_force, b->d_force, 4 * b->n * sizeof(double),
-                                hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  hipError_t e = hipStreamSynchronize(s);
   if (e != hipSuccess) return bhip(b, e, "force read-back");
   for (int i = 0; i < b->n; ++i)
     for (int k = 0; k < 3; ++k) out[3 * i + k] = b->h_force[4 * i + k];

@@ -29,8 +29,6 @@ namespace dgmi {
 
 namespace {
 
-constexpr int kCflThreads = 256;
-
 // Node j (counter-clockwise) of face f in the reference node numbering
 // (rows of the numbering start at i(N+1) - i(i-1)/2).
 template <int N>
@@ -54,8 +52,7 @@ template <int N>
 __global__ __launch_bounds__(kCflThreads) void cfl_local_kernel(DeviceTables t, KernelPhysics ph,
                                                                 const double* __restrict__ U,
                                                                 double* __restrict__ side,
-                                                                double* __restrict__ loc,
-                                                                double* __restrict__ result) {
+                                                                double* __restrict__ loc) {
   constexpr int Np = (N + 1) * (N + 2) / 2, Nfp = N + 1, NF = 3 * Nfp;
   constexpr int EPB = kCflThreads / Np;
   __shared__ double su[EPB * Np], sv[EPB * Np], sb[EPB * Np], sg[EPB * Np], sd[EPB * Np];
@@ -63,7 +60,6 @@ __global__ __launch_bounds__(kCflThreads) void cfl_local_kernel(DeviceTables t, 
   const int e = threadIdx.x / Np, n = threadIdx.x % Np;
   const int64_t k = (int64_t)blockIdx.x * EPB + e;
   const bool act = e < EPB && k < t.K;
-  if (blockIdx.x == 0 && threadIdx.x == 0) result[0] = 0.0;
   Gas<double> gas;
   gas.gamma = ph.gamma;
   gas.gm1 = ph.gamma - 1.0;
@@ -141,7 +137,7 @@ __global__ __launch_bounds__(kCflThreads) void cfl_local_kernel(DeviceTables t, 
 __global__ __launch_bounds__(kCflThreads) void cfl_reduce_kernel(DeviceTables t, int N, double C_grad,
                                                                  const double* __restrict__ side,
                                                                  const double* __restrict__ loc,
-                                                                 double* __restrict__ result) {
+                                                                 double* __restrict__ parts) {
   __shared__ double part[kCflThreads / 64];
   const int64_t k = (int64_t)blockIdx.x * kCflThreads + threadIdx.x;
   double lam = 0.0;
@@ -171,27 +167,24 @@ __global__ __launch_bounds__(kCflThreads) void cfl_reduce_kernel(DeviceTables t,
   if (threadIdx.x == 0) {
     double m = part[0];
     for (int w = 1; w < kCflThreads / 64; ++w) m = vmax(m, part[w]);
-    // non-negative doubles order as their bit patterns (a NaN compares
-    // above every finite value and is reported by the caller)
-    atomicMax((unsigned long long*)result, (unsigned long long)__double_as_longlong(m));
+    parts[blockIdx.x] = m;
   }
 }
 
 template <int N>
 int launch_cfl_n(const DeviceTables& t, const KernelPhysics& ph, const double* U, double C_grad,
-                 double* work, hipStream_t s, std::string& err) {
+                 double* work, double* parts, hipStream_t s, std::string& err) {
   constexpr int EPB = kCflThreads / ((N + 1) * (N + 2) / 2);
   const unsigned lblocks = (unsigned)((t.K + EPB - 1) / EPB);
-  const unsigned blocks = (unsigned)((t.K + kCflThreads - 1) / kCflThreads);
+  const unsigned blocks = (unsigned)cfl_blocks(t.K);
   double* side = work;
   double* loc = work + 3 * t.K;
-  double* result = work + 6 * t.K;
   hipLaunchKernelGGL(cfl_local_kernel<N>, dim3(lblocks), dim3(kCflThreads), 0, s, t, ph, U, side,
-                     loc, result);
+                     loc);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) {
     hipLaunchKernelGGL(cfl_reduce_kernel, dim3(blocks), dim3(kCflThreads), 0, s, t, N, C_grad, side,
-                       loc, result);
+                       loc, parts);
     e = hipGetLastError();
   }
   if (e != hipSuccess) {
@@ -203,22 +196,22 @@ int launch_cfl_n(const DeviceTables& t, const KernelPhysics& ph, const double* U
 
 }  // namespace
 
-size_t cfl_work_size(int64_t K) { return (size_t)(6 * K + 1); }
+size_t cfl_work_size(int64_t K) { return (size_t)(6 * K); }
 
 int launch_cfl(int N, const DeviceTables& t, const KernelPhysics& ph, const double* U, double C_grad,
-               double* work, void* stream, std::string& err) {
+               double* work, double* parts, void* stream, std::string& err) {
   if (t.K <= 0) {
     err = "empty mesh";
     return -1;
   }
   hipStream_t s = (hipStream_t)stream;
   switch (N) {
-    case 1: return launch_cfl_n<1>(t, ph, U, C_grad, work, s, err);
-    case 2: return launch_cfl_n<2>(t, ph, U, C_grad, work, s, err);
-    case 3: return launch_cfl_n<3>(t, ph, U, C_grad, work, s, err);
-    case 4: return launch_cfl_n<4>(t, ph, U, C_grad, work, s, err);
-    case 5: return launch_cfl_n<5>(t, ph, U, C_grad, work, s, err);
-    case 6: return launch_cfl_n<6>(t, ph, U, C_grad, work, s, err);
+    case 1: return launch_cfl_n<1>(t, ph, U, C_grad, work, parts, s, err);
+    case 2: return launch_cfl_n<2>(t, ph, U, C_grad, work, parts, s, err);
+    case 3: return launch_cfl_n<3>(t, ph, U, C_grad, work, parts, s, err);
+    case 4: return launch_cfl_n<4>(t, ph, U, C_grad, work, parts, s, err);
+    case 5: return launch_cfl_n<5>(t, ph, U, C_grad, work, parts, s, err);
+    case 6: return launch_cfl_n<6>(t, ph, U, C_grad, work, parts, s, err);
     default: err = "order outside 1..6"; return -5;
   }
 }

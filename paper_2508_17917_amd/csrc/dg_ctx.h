@@ -51,13 +51,14 @@ struct dg_ctx {
   int32_t* d_wall = nullptr;
   double* d_wall_xy = nullptr;
   double* d_scratch = nullptr;
+  double* d_scratch2 = nullptr;   // a second scratch state (null: an odd number of stages ends with a copy)
   void* d_trace[2] = {nullptr, nullptr};  // face traces of a stage's input and output (null: none)
   size_t trace_size = 0;                  // bytes of each
-  double* d_force = nullptr;
+  double* h_force = nullptr;        // pinned: partials of the force the host sums
   double* d_force_part = nullptr;
   unsigned* d_force_ticket = nullptr;
-  double* d_cfl = nullptr;          // CFL work: 3K face maxima, 3K element maxima, result
-  double* h_cfl = nullptr;          // pinned host word for the CFL result
+  double* d_cfl = nullptr;          // CFL work: 3K face maxima, 3K element maxima
+  double* h_cfl = nullptr;          // pinned: the CFL bound's maxima by workgroup
   double* noalloc_scratch = nullptr;  // this device's static scratch array (not owned)
   // isoparametric elements given by dg_set_curved_elements, and their tables
   std::vector<int32_t> curved_elems;
@@ -101,6 +102,24 @@ struct Stages {
     return rc;
   }
 };
+// The state buffers of one call's stages: U and a scratch state in turn.  An odd
+// number of stages goes U, S, S2, U at its start where there is a second scratch
+// state, and so ends in U; else it ends in the scratch state (in_scratch).
+struct StateBuffers {
+  double *U, *S, *S2;
+  bool odd;
+  StateBuffers(double* u, double* s, double* s2, int64_t stages) : U(u), S(s), S2(stages >= 3 ? s2 : nullptr), odd(stages & 1) {}
+  // the state before stage i, which is the output of stage i - 1
+  double* at(int64_t i) const {
+    if (odd && S2) return i < 3 ? (i == 0 ? U : (i == 1 ? S : S2)) : ((i & 1) ? U : S);
+    return (i & 1) ? S : U;
+  }
+  bool in_scratch() const { return odd && !S2; }
+};
+// The largest state that gets a second scratch state: beyond it the copy that
+// this saves is 3 % of a step's five stages (20,480 elements at p = 4: 3 of 90
+// us; the smaller the mesh, the more: 5,120 at p = 3: 3 us and a launch of 62).
+constexpr size_t kSecondScratch = (size_t)64 << 20;
 // Face traces serve straight-sided meshes (the stage launch evaluates curved
 // elements and their neighbours in FP64 beside the straight tiles) in every
 // form but bfloat16 operators.  Over-integration switched on after the set-up

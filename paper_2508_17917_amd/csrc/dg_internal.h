@@ -263,11 +263,14 @@ int force_blocks_for(int N, int nwall);
 // workgroups (items in device memory, block ranges consecutive from 0)
 int launch_batch_force(int N, const ForceItem* items, int count, int blocks, void* stream,
                        std::string& err);
-// cfl.hip: Lambda of the CFL bound on the state U into work[6K] (work holds
-// cfl_work_size(K) doubles)
+// cfl.hip: Lambda of the CFL bound on the state U as one maximum per workgroup,
+// parts[cfl_blocks(K)] (device-visible); work holds cfl_work_size(K) doubles
+constexpr int kCflThreads = 256;
+inline int64_t cfl_blocks(int64_t K) { return (K + kCflThreads - 1) / kCflThreads; }
 size_t cfl_work_size(int64_t K);
 int launch_cfl(int N, const DeviceTables& t, const KernelPhysics& ph, const double* U, double C_grad,
-               double* work, void* stream, std::string& err);
+               double* work, double* parts, void* stream, std::string& err);
+// out_dev null: the partials alone, into t.force_part
 int launch_force(int N, const DeviceTables& t, const KernelPhysics& ph, const double* U,
                  double* out_dev, void* stream, std::string& err);
 // operator packing: Dr | Ds | LIFT | LIFTr | LIFTs | wface

@@ -29,13 +29,14 @@ int hip_fail(dg_ctx* c, hipError_t e, const char* what) {
 
 void free_device(dg_ctx* c) {
   void* ptrs[] = {c->d_geo,  c->d_conn,    c->d_ops,     c->d_frag,       c->d_frag32,
-                  c->d_frag16, c->d_wall, c->d_wall_xy, c->d_scratch, c->d_force,
+                  c->d_frag16, c->d_wall, c->d_wall_xy, c->d_scratch, c->d_scratch2,
                   c->d_force_part, c->d_force_ticket, c->d_oi, c->d_cfl,
                   c->d_cslot, c->d_celem, c->d_cnode, c->d_cface, c->d_cP, c->d_trace[0], c->d_trace[1]};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (c->h_cfl) (void)hipHostFree(c->h_cfl);
-  c->h_cfl = nullptr;
+  if (c->h_force) (void)hipHostFree(c->h_force);
+  c->h_cfl = c->h_force = nullptr;
   c->d_geo = nullptr;
   c->d_conn = nullptr;
   c->d_ops = nullptr;
@@ -44,8 +45,7 @@ void free_device(dg_ctx* c) {
   c->d_frag16 = nullptr;
   c->d_wall = nullptr;
   c->d_wall_xy = nullptr;
-  c->d_scratch = nullptr;
-  c->d_force = nullptr;
+  c->d_scratch = c->d_scratch2 = nullptr;
   c->d_force_part = nullptr;
   c->d_force_ticket = nullptr;
   c->d_oi = nullptr;
@@ -279,15 +279,20 @@ int dg_setup(dg_ctx* c) {
   c->force_blocks = dgmi::force_blocks_for(c->N, (int)c->mesh.wall_faces.size());
   const int fb = c->force_blocks > 0 ? c->force_blocks : 1;
   if ((e = hipMalloc((void**)&c->d_scratch, state)) != hipSuccess ||
-      (e = hipMalloc((void**)&c->d_force, 4 * sizeof(double))) != hipSuccess ||
       (e = hipMalloc((void**)&c->d_force_part, 3 * fb * sizeof(double))) != hipSuccess ||
       (e = hipMalloc((void**)&c->d_force_ticket, sizeof(unsigned))) != hipSuccess ||
       (e = hipMalloc((void**)&c->d_cfl, dgmi::cfl_work_size(c->K) * sizeof(double))) != hipSuccess ||
-      (e = hipHostMalloc((void**)&c->h_cfl, sizeof(double), hipHostMallocDefault)) != hipSuccess ||
+      (e = hipHostMalloc((void**)&c->h_cfl, dgmi::cfl_blocks(c->K) * sizeof(double), hipHostMallocDefault)) != hipSuccess ||
+      (e = hipHostMalloc((void**)&c->h_force, 3 * fb * sizeof(double), hipHostMallocDefault)) != hipSuccess ||
       (e = hipMemset(c->d_force_ticket, 0, sizeof(unsigned))) != hipSuccess) {
     free_device(c);
     return e == hipErrorOutOfMemory ? fail(c, DG_ENOMEM, "device allocation failed")
                                     : hip_fail(c, e, "hipMalloc");
+  }
+  // a second scratch state for an odd number of stages; without it they end with a copy
+  if (state <= dgmi::kSecondScratch && hipMalloc((void**)&c->d_scratch2, state) != hipSuccess) {
+    c->d_scratch2 = nullptr;
+    (void)hipGetLastError();
   }
   // face traces of a stage's input and output; without the memory for them the
   // stages run from the neighbours' states
@@ -415,17 +420,19 @@ int dg_rk_step(dg_ctx* c, double* U, double* K1, double dt, const double v_w[2],
   std::string err;
   dgmi::DeviceTables t = tables(c);
   dgmi::KernelPhysics k = kphys(c, v_w);
-  double* bufs[2] = {U, c->d_scratch};
+  const dgmi::StateBuffers bufs(U, c->d_scratch, c->d_scratch2, 5);
   dgmi::Stages stages = dgmi::ctx_stages(c, 1);
   rc = stages.begin(t, k, U, stream, err);
   if (rc != 0) return fail(c, rc, err);
   for (int i = 0; i < 5; ++i) {
-    rc = stages.run(t, k, bufs[i & 1], bufs[(i + 1) & 1], K1, i, dt, i == 4, stream, err);
+    rc = stages.run(t, k, bufs.at(i), bufs.at(i + 1), K1, i, dt, i == 4, stream, err);
     if (rc != 0) return fail(c, rc, err);
   }
-  size_t bytes = (size_t)c->K * 4 * c->ref.Np * sizeof(double);
-  hipError_t e = hipMemcpyAsync(U, c->d_scratch, bytes, hipMemcpyDeviceToDevice, (hipStream_t)stream);
-  if (e != hipSuccess) return hip_fail(c, e, "hipMemcpyAsync");
+  if (bufs.in_scratch()) {
+    const size_t bytes = (size_t)c->K * 4 * c->ref.Np * sizeof(double);
+    hipError_t e = hipMemcpyAsync(U, c->d_scratch, bytes, hipMemcpyDeviceToDevice, (hipStream_t)stream);
+    if (e != hipSuccess) return hip_fail(c, e, "hipMemcpyAsync");
+  }
   return DG_OK;
 }
 
@@ -440,16 +447,13 @@ int dg_rk_steps(dg_ctx* c, double* U, double* K1, int nsteps, double dt, const d
   const dgmi::DeviceTables t = tables(c);
   const dgmi::KernelPhysics k = kphys(c, v_w);
   const bool walls = !c->mesh.wall_faces.empty();
-  // the state alternates between U and the scratch buffer: five stages per
-  // step, so it sits in the other buffer after every step
-  double* bufs[2] = {U, c->d_scratch};
+  const dgmi::StateBuffers bufs(U, c->d_scratch, c->d_scratch2, 5 * (int64_t)nsteps);
   // the force after step n: its partials by leading waves of step n + 1's
   // first stage launch, whose input is that state, their sum in block order
   // by a leading wave of the second (the nodal stage kernel; the
   // over-integrated stage launches it apart); the last step's by a launch of
   // its own
   const bool fuse = force_dev && walls && !c->overint;
-  int cur = 0;
   dgmi::Stages stages = dgmi::ctx_stages(c, nsteps);
   if (nsteps > 0 && (rc = stages.begin(t, k, U, stream, err)) != 0) return fail(c, rc, err);
   for (int n = 0; n < nsteps; ++n) {
@@ -457,17 +461,17 @@ int dg_rk_steps(dg_ctx* c, double* U, double* K1, int nsteps, double dt, const d
       dgmi::DeviceTables ti = t;
       if (fuse && n > 0 && i == 0) ti.force_parts = true;
       if (fuse && n > 0 && i == 1) ti.force_fin = force_dev + 3 * (int64_t)(n - 1);
-      rc = stages.run(ti, k, bufs[(cur + i) & 1], bufs[(cur + i + 1) & 1], K1, i, dt,
-                      n == nsteps - 1 && i == 4, stream, err);
+      const int64_t st = 5 * (int64_t)n + i;
+      rc = stages.run(ti, k, bufs.at(st), bufs.at(st + 1), K1, i, dt, n == nsteps - 1 && i == 4, stream, err);
       if (rc != 0) return fail(c, rc, err);
     }
-    cur ^= 1;
+    const double* Un = bufs.at(5 * (int64_t)(n + 1));
     if (fuse && n == nsteps - 1) {
-      rc = dgmi::launch_force(c->N, t, k, bufs[cur], force_dev + 3 * (int64_t)n, stream, err);
+      rc = dgmi::launch_force(c->N, t, k, Un, force_dev + 3 * (int64_t)n, stream, err);
       if (rc != 0) return fail(c, rc, err);
     } else if (force_dev && !fuse) {
       if (walls) {
-        rc = dgmi::launch_force(c->N, t, k, bufs[cur], force_dev + 3 * (int64_t)n, stream, err);
+        rc = dgmi::launch_force(c->N, t, k, Un, force_dev + 3 * (int64_t)n, stream, err);
         if (rc != 0) return fail(c, rc, err);
       } else {
         hipError_t e = hipMemsetAsync(force_dev + 3 * (int64_t)n, 0, 3 * sizeof(double),
@@ -476,7 +480,7 @@ int dg_rk_steps(dg_ctx* c, double* U, double* K1, int nsteps, double dt, const d
       }
     }
   }
-  if (cur == 1) {
+  if (bufs.in_scratch()) {
     const size_t bytes = (size_t)c->K * 4 * c->ref.Np * sizeof(double);
     hipError_t e = hipMemcpyAsync(U, c->d_scratch, bytes, hipMemcpyDeviceToDevice, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(c, e, "hipMemcpyAsync");
@@ -493,16 +497,19 @@ int dg_force(dg_ctx* c, const double* U, const double v_w[2], double out[3], voi
     return DG_OK;
   }
   std::string err;
-  rc = dgmi::launch_force(c->N, tables(c), kphys(c, v_w), U, c->d_force, stream, err);
+  // the partials land in pinned memory and are added here in the order in which
+  // launch_force's last wave adds them
+  dgmi::DeviceTables t = tables(c);
+  t.force_part = c->h_force;
+  rc = dgmi::launch_force(c->N, t, kphys(c, v_w), U, nullptr, stream, err);
   if (rc != 0) return fail(c, rc, err);
-  double h[3];
-  hipError_t e = hipMemcpyAsync(h, c->d_force, 3 * sizeof(double), hipMemcpyDeviceToHost,
-                                (hipStream_t)stream);
-  if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
+  hipError_t e = hipStreamSynchronize((hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(c, e, "force read-back");
-  out[0] = h[0];
-  out[1] = h[1];
-  out[2] = h[2];
+  for (int i = 0; i < 3; ++i) {
+    double sum = 0.0;
+    for (int b = 0; b < c->force_blocks; ++b) sum += c->h_force[3 * b + i];
+    out[i] = sum;
+  }
   return DG_OK;
 }
 
@@ -513,13 +520,20 @@ int dg_cfl_time_step(dg_ctx* c, const double* U, const double v_w[2], double C_c
   if (!U || !out) return fail(c, DG_EINVAL, "NULL argument");
   if (!(C_cfl > 0.0) || !(C_grad >= 0.0)) return fail(c, DG_EINVAL, "C_cfl must be > 0, C_grad >= 0");
   std::string err;
-  rc = dgmi::launch_cfl(c->N, tables(c), kphys(c, v_w), U, C_grad, c->d_cfl, stream, err);
+  rc = dgmi::launch_cfl(c->N, tables(c), kphys(c, v_w), U, C_grad, c->d_cfl, c->h_cfl, stream, err);
   if (rc != 0) return fail(c, rc, err);
-  hipError_t e = hipMemcpyAsync(c->h_cfl, c->d_cfl + 6 * c->K, sizeof(double),
-                                hipMemcpyDeviceToHost, (hipStream_t)stream);
-  if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
+  hipError_t e = hipStreamSynchronize((hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(c, e, "CFL read-back");
-  const double lam = *c->h_cfl;
+  // the largest of the workgroups' maxima by their bit patterns, in which
+  // non-negative doubles are ordered and a NaN is above every number
+  uint64_t top = 0;
+  for (int64_t b = 0, n = dgmi::cfl_blocks(c->K); b < n; ++b) {
+    uint64_t bits;
+    std::memcpy(&bits, c->h_cfl + b, sizeof bits);
+    if (bits > top) top = bits;
+  }
+  double lam;
+  std::memcpy(&lam, &top, sizeof lam);
   if (!std::isfinite(lam) || !(lam > 0.0)) return fail(c, DG_ENONFINITE, "CFL bound is not finite and positive");
   out[0] = lam;
   out[1] = C_cfl / lam;

@@ -1330,19 +1330,13 @@ batch_order_kernel(const BatchItem* __restrict__ items, const BatchStep* __restr
 // partials, and the last workgroup to finish (an atomic ticket) sums the
 // partials in workgroup order and resets the ticket: deterministic, one
 // launch, no host synchronisation and no wait inside the kernel.
-// Workgroup blk of the nblk that cover one mesh's wall face nodes.
-template <int N>
-__device__ __forceinline__ void force_block(const DeviceTables& t, const KernelPhysics& ph,
-                                            const double* __restrict__ U, double* __restrict__ out,
-                                            unsigned blk, unsigned nblk) {
-  force_wave<N>(t, ph, U, out, blk, nblk);
-}
-
-template <int N>
+// out null: the partials alone, for a caller who adds them (blocks of 64 nodes,
+// in order) on the host, t.force_part then being memory that the host reads.
+template <int N, bool TICKET>
 __global__ __launch_bounds__(kForceThreads) void force_kernel(DeviceTables t, KernelPhysics ph,
                                                               const double* __restrict__ U,
                                                               double* __restrict__ out) {
-  force_block<N>(t, ph, U, out, blockIdx.x, gridDim.x);
+  force_wave<N, (N + 1) * (N + 2) / 2, TICKET>(t, ph, U, out, blockIdx.x, gridDim.x);
 }
 
 // Many meshes of one order: instance i owns the workgroups
@@ -1354,7 +1348,7 @@ __global__ __launch_bounds__(kForceThreads) void batch_force_kernel(const ForceI
   int i = 0;
   while (i + 1 < count && (int)blockIdx.x >= items[i + 1].block_begin) ++i;
   const ForceItem& it = items[i];
-  force_block<N>(it.t, it.ph, it.U, it.out, blockIdx.x - it.block_begin, it.nblocks);
+  force_wave<N>(it.t, it.ph, it.U, it.out, blockIdx.x - it.block_begin, it.nblocks);
 }
 
 namespace {
@@ -1449,7 +1443,10 @@ int launch_force_n(const DeviceTables& t, const KernelPhysics& ph, const double*
     err = "wall force: workgroup count outside the set-up partial buffer";
     return -1;
   }
-  hipLaunchKernelGGL(force_kernel<N>, dim3(blocks), dim3(kForceThreads), 0, s, t, ph, U, out);
+  if (out)
+    hipLaunchKernelGGL((force_kernel<N, true>), dim3(blocks), dim3(kForceThreads), 0, s, t, ph, U, out);
+  else
+    hipLaunchKernelGGL((force_kernel<N, false>), dim3(blocks), dim3(kForceThreads), 0, s, t, ph, U, out);
   return launch_error(err, "force kernel launch");
 }
 
