@@ -268,13 +268,20 @@ __device__ __noinline__ double sym3_lambda_max_trig(double s00, double s11, doub
   return q + 2.0 * pp * cos(acos(r) * (1.0 / 3.0));
 }
 
+// An upper bound of sqrt(x), close to it (binary64: the hardware estimate of the
+// reciprocal root, good to 6e-8, raised by 2e-7).
+__device__ __forceinline__ double upper_root(double x) {
+  return x * (__builtin_amdgcn_rsq(x) * 1.0000002);
+}
+__device__ __forceinline__ float upper_root(float x) { return root(x); }
+
 // ||A||_2 for A = nx^2 G11 + nx ny (G12 + G21) + ny^2 G22.  The first row of
 // A is zero, so ||A||_2 = (mu/rho) sqrt(lambda_max(B B^T)) for the 3x4 block B
 // of its lower rows.  lambda_max of the symmetric positive semi-definite
 // S = B B^T: Newton on its characteristic cubic from the Frobenius norm of S,
 // an upper bound within a few per cent of lambda_max when the top eigenvalue
 // is well separated (iterates decrease monotonically to the largest root).
-// If the last step is not negligible -- a near-double top eigenvalue, where
+// If the last step is too large -- a near-double top eigenvalue, where
 // Newton converges only linearly -- the closed-form trigonometric solution is
 // used instead.
 template <typename T>
@@ -303,13 +310,10 @@ __device__ __forceinline__ T normal_diffusion_norm(const Gas<T>& g, const VState
   const T c1 = s00 * s11 + s00 * s22 + s11 * s22 - s01 * s01 - s02 * s02 - s12 * s12;
   const T c0 = s00 * (s11 * s22 - s12 * s12) - s01 * (s01 * s22 - s12 * s02) +
                s02 * (s01 * s12 - s11 * s02);
-  T lam = root(s00 * s00 + s11 * s11 + s22 * s22 + T(2) * (s01 * s01 + s02 * s02 + s12 * s12));
+  const T fro2 = s00 * s00 + s11 * s11 + s22 * s22 + T(2) * (s01 * s01 + s02 * s02 + s12 * s12);
+  T lam = upper_root(fro2);
   T step = T(0);
-  // quadratic convergence from the close upper bound: three steps reach the
-  // binary32 tolerance, five the binary64 one (else the fallback below)
-  constexpr int kIters = sizeof(T) == 8 ? 5 : 3;
-#pragma unroll
-  for (int it = 0; it < kIters; ++it) {
+  auto newton = [&] {
     const T f = ((lam - c2) * lam + c1) * lam - c0;
     const T df = (T(3) * lam - T(2) * c2) * lam + c1;
     // the step only needs an approximate reciprocal: Newton corrects the rest
@@ -317,11 +321,22 @@ __device__ __forceinline__ T normal_diffusion_norm(const Gas<T>& g, const VState
     r = r * (T(2) - df * r);
     step = (df > T(0)) ? f * r : T(0);
     lam -= step;
+  };
+  // quadratic convergence from the close upper bound: three steps reach the
+  // binary32 tolerance, four the binary64 one: a fourth step below 1e-10 leaves its
+  // square times lambda over the gap to the next eigenvalue, nothing that binary64
+  // holds (12 ranges of states, 400,000 each, against extended precision: at most
+  // 4.9e-16, where a fifth step below 1e-15 leaves up to 6.4e-16).  Others take a
+  // fifth.  20,480 elements, 200 stages at p = 2: 3,523 us with five steps from
+  // the refined root of the Frobenius norm, 3,445 so.
+#pragma unroll
+  for (int it = 0; it < (sizeof(T) == 8 ? 4 : 3); ++it) newton();
+  if (!(fabs(step) <= (sizeof(T) == 8 ? T(1e-10) : T(1e-6)) * lam)) {
+    if constexpr (sizeof(T) == 8) newton();
+    if (sizeof(T) == 4 || !(fabs(step) <= T(1e-15) * lam))
+      lam = (T)sym3_lambda_max_trig((double)s00, (double)s11, (double)s22, (double)s01, (double)s02,
+                                    (double)s12);
   }
-  const T tol = (sizeof(T) == 8) ? T(1e-15) : T(1e-6);
-  if (!(fabs(step) <= tol * lam))
-    lam = (T)sym3_lambda_max_trig((double)s00, (double)s11, (double)s22, (double)s01, (double)s02,
-                                  (double)s12);
   return st.m * root(lam > T(0) ? lam : T(0));
 }
 
