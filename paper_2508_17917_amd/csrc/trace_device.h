@@ -72,11 +72,12 @@ struct TraceOrder {
   static constexpr int WAVES = 4;
   // registers: three waves per SIMD in FP32, two in FP64 (four and three spill:
   // p = 4 FP32 16.4 -> 18.1 us, FP64 22.6 -> 24.6).  K1 / K0 are loaded before the
-  // face pass where they fit beside it (p = 3, 4); at p = 5 in FP32 they spill
-  // there (28 -> 35 us).  The next tile's own data come after the face pass
-  // everywhere (before it: p = 4 FP32 16.4 -> 16.8 us, p = 6 FP64 +2 %).
+  // face pass where they fit beside it (p <= 4; after it, p = 2 FP64 on 20,480
+  // elements 17.6 -> 17.9); at p = 5 in FP32 they spill there (28 -> 35 us).  The
+  // next tile's own data come after the face pass everywhere (before it: p = 4
+  // FP32 16.4 -> 16.8 us, p = 6 FP64 +2 %).
   static constexpr int MIN_WAVES_EU = sizeof(T) == 4 ? 3 : 2;
-  static constexpr bool EARLY_K = N == 3 || N == 4;
+  static constexpr bool EARLY_K = N <= 4;
 };
 
 // Stores of a LARGE launch (the stage's arrays exceed the last-level cache) do
