@@ -182,7 +182,7 @@ def oi_flops_per_element(Np, Nfp):
 def kernel_sources_hash():
     import hashlib
     h = hashlib.sha256()
-    for f in ("kernels.hip", "trace.hip", "trace_batch.hip", "oi_trace.hip", "trace_device.h", "stage_device.h", "dg_physics.h"):
+    for f in ("kernels.hip", "trace.hip", "trace_batch.hip", "oi_trace.hip", "trace_device.h", "curved_device.h", "stage_device.h", "dg_physics.h"):
         with open(os.path.join(ROOT, "paper_2508_17917_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

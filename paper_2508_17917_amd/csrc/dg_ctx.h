@@ -120,12 +120,14 @@ struct StateBuffers {
 // this saves is 3 % of a step's five stages (20,480 elements at p = 4: 3 of 90
 // us; the smaller the mesh, the more: 5,120 at p = 3: 3 us and a launch of 62).
 constexpr size_t kSecondScratch = (size_t)64 << 20;
-// Face traces serve straight-sided meshes (the stage launch evaluates curved
-// elements and their neighbours in FP64 beside the straight tiles) in every
-// form but bfloat16 operators.  Over-integration switched on after the set-up
-// finds arrays of the nodal size and runs without them.
+// Face traces serve every form but bfloat16 operators, and meshes with curved
+// elements where the stage's arrays fit the last-level cache (beyond it the
+// stages run from the neighbours' states).  Over-integration switched on after
+// the set-up finds arrays of the nodal size and runs without them.
 inline size_t ctx_trace_bytes(const dg_ctx* c) {
-  return c->mesh.celem.empty() ? trace_bytes(c->N, ctx_form(c), c->K) : 0;
+  const int form = ctx_form(c);
+  if (!c->mesh.celem.empty() && (form == kFormOverint || beyond_cache(trace_stage_bytes(c->N, form, c->K)))) return 0;
+  return trace_bytes(c->N, form, c->K);
 }
 // Whether nsteps steps on K elements (of one mesh or a batch) run from traces:
 // the launch that makes the first ones costs 6 us on a small mesh, which the

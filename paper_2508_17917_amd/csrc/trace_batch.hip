@@ -37,7 +37,7 @@ __device__ __forceinline__ void batch_trace_group(const BatchItem* __restrict__ 
   using P = TraceOrder<N, T, LARGE>;
   T* sFrag = (T*)smem;
   T* sWave = sFrag + O::FRAG_SZ;
-  trace_lds_init<N, T, W, O::FRAG_SZ, LARGE>(frag_table<T>(items[g.first_item].t), sFrag, sWave);
+  trace_lds_init<N, T, W, O::FRAG_SZ, LARGE, TraceOrder<N, T, LARGE>::WAVE_SZ>(frag_table<T>(items[g.first_item].t), sFrag, sWave);
   T* area = sWave + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * P::WAVE_SZ;
   for_items<W>(items, g, [&](int i, int tile0, int tile_end, int stride) {
     const BatchItem& it = items[i];
@@ -45,7 +45,7 @@ __device__ __forceinline__ void batch_trace_group(const BatchItem* __restrict__ 
     ph.vw[0] = steps[i].vw[0];
     ph.vw[1] = steps[i].vw[1];
     const int src = (par + stage) & 1;
-    trace_tiles<N, T, PERT, LARGE>(it.t, ph, it.buf[src], it.buf[src ^ 1], it.K1, a, b, steps[i].dt,
+    trace_tiles<N, T, PERT, LARGE, false>(it.t, ph, it.buf[src], it.buf[src ^ 1], it.K1, a, b, steps[i].dt,
                                    (const V4*)it.tr[src], (V4*)it.tr[src ^ 1], sFrag, area, tile0, tile_end, stride, [] {});
   });
 }
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256) void batch_face_trace_kernel(const BatchItem* 
   using P = TraceOrder<N, T, LARGE>;
   __shared__ __attribute__((aligned(16))) T sFrag[2 * O::FD];
   __shared__ __attribute__((aligned(16))) T sWave[W * P::WAVE_SZ];
-  trace_lds_init<N, T, W, 2 * O::FD, LARGE>(frag_table<T>(items[g.first_item].t), sFrag, sWave);
+  trace_lds_init<N, T, W, 2 * O::FD, LARGE, TraceOrder<N, T, LARGE>::WAVE_SZ>(frag_table<T>(items[g.first_item].t), sFrag, sWave);
   T* area = sWave + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * P::WAVE_SZ;
   const int par = parity[0];
   for_items<W>(items, g, [&](int i, int tile0, int tile_end, int stride) {

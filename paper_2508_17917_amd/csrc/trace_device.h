@@ -211,12 +211,13 @@ __device__ __forceinline__ void zero_pads(T* rows0, int rows, int lane) {
 
 // The traces of the states staged in sU (synced): one lane per face node of
 // the tile's nel elements.  Boundary faces carry the wall's or the far field's
-// viscous flux, and the ghost's norm in the maximum.
+// viscous flux, and the ghost's norm in the maximum.  skip: the slots (bits) whose
+// traces another wave writes.
 template <int N, typename T, bool PERT, bool LARGE>
 __device__ __forceinline__ void write_traces(const FaceConst<T>& fc, const FaceLane<N, T, LARGE>& fl,
                                              const T* sU, const T* sGeo, T* sNorm, const T* sFrag,
                                              int lane, int conn, int nel, int64_t e0,
-                                             typename Vec4<T>::type* __restrict__ tr) {
+                                             typename Vec4<T>::type* __restrict__ tr, unsigned skip = 0) {
   using P = TraceOrder<N, T, LARGE>;
   T gxk[P::G][P::NT][4], gyk[P::G][P::NT][4];
   tile_gradient<N, T, LARGE>(sU, sGeo, sFrag, lane, nel, gxk, gyk);
@@ -255,7 +256,7 @@ __device__ __forceinline__ void write_traces(const FaceConst<T>& fc, const FaceL
     sNorm[lane] = nrm;
   }
   wave_sync();
-  if (ok) {
+  if (ok && !((skip >> fl.e) & 1)) {
     T gmax = T(0);
 #pragma unroll
     for (int jj = 0; jj < P::Nfp; ++jj) {
@@ -270,8 +271,9 @@ __device__ __forceinline__ void write_traces(const FaceConst<T>& fc, const FaceL
 // run by one wavefront: traces tr_in of Uin in, and unless tr_out is null
 // those of the new state out.  `lds_init` runs once, after the first tile's
 // loads are issued (the workgroup's operator fragments, whose latency the
-// loads then share).
-template <int N, typename T, bool PERT, bool LARGE, typename Init>
+// loads then share).  CURVED: the elements of the curved set, whose outputs and
+// traces other waves write, are left out of a tile's stores.
+template <int N, typename T, bool PERT, bool LARGE, bool CURVED, typename Init>
 __device__ __forceinline__ void trace_tiles(const DeviceTables& t, const KernelPhysics& ph,
                                             const double* __restrict__ Uin,
                                             double* __restrict__ Uout, double* __restrict__ K1,
@@ -366,9 +368,13 @@ __device__ __forceinline__ void trace_tiles(const DeviceTables& t, const KernelP
     // the face node's other side: its state (4 strided values) and its trace;
     // a boundary face points at the element itself
     const bool okf = lane < nel * NF;
+    // slots of the curved set
+    unsigned skip = 0;
+    if constexpr (CURVED) skip = (unsigned)__ballot(lane < nel && t.cslot[e0 + (lane < nel ? lane : 0)] >= 0);
+    auto kept = [&](int e) { return !CURVED || !((skip >> e) & 1); };
     const int conn = __builtin_amdgcn_ds_bpermute((fl.e * 3 + fl.f) << 2, rc);
     const int tag = conn & 3;
-    const V4 own = rt;
+    V4 own = rt;
     double un[4];
     V4 nbt;
     {
@@ -381,6 +387,10 @@ __device__ __forceinline__ void trace_tiles(const DeviceTables& t, const KernelP
       for (int c = 0; c < 4; ++c) un[c] = up[c * Np];
       nbt = tr_in[ne * NF + mfo * Nfp + mj];
     }
+    // between elements of the set no traces are written: what those lanes read may
+    // be anything, and what they make must stay finite (the next tile's products
+    // read some of it against zeros)
+    if (!kept(fl.e)) own = nbt = V4{T(0), T(0), T(0), T(0)};
     wave_sync();
 
     // ---- gradient on the matrix cores, volume flux per node, contravariant
@@ -572,8 +582,8 @@ __device__ __forceinline__ void trace_tiles(const DeviceTables& t, const KernelP
 #pragma unroll
     for (int i = 0; i < NO; ++i) {
       const int at = P::FLAT ? lds_u[P::FLAT ? i : 0] : row_of<N, T, LARGE>(i, re) * RS + rn;
-      const bool in = P::FLAT ? lane + 64 * i < nel * S : (re < nel && rn < Np);
-      if (in) {
+      const bool in = (P::FLAT ? lane + 64 * i < nel * S : (re < nel && rn < Np));
+      if (in && kept(P::FLAT ? (lane + 64 * i) / S : re)) {
         const double R = (double)(P::FLAT ? sH[at] : aD[0][0][P::FLAT ? 0 : i]);
         const int64_t idx = e0 * S + out_off(i);
         const double k = (a != 0.0) ? a * rk[i] + dt * R : dt * R;
@@ -594,18 +604,18 @@ __device__ __forceinline__ void trace_tiles(const DeviceTables& t, const KernelP
       }
       if constexpr (P::OVER) zero_pads<N, T>(sU, G * 16, lane);
       wave_sync();
-      write_traces<N, T, PERT, LARGE>(fc, fl, sU, sGeo, sNorm, sFrag, lane, conn, nel, e0, tr_out);
+      write_traces<N, T, PERT, LARGE>(fc, fl, sU, sGeo, sNorm, sFrag, lane, conn, nel, e0, tr_out, skip);
     }
   }
 }
 
 // Copy COUNT operator fragment values into LDS and zero the pad columns of the
 // workgroup's state and flux rows.
-template <int N, typename T, int W, int COUNT, bool LARGE>
+template <int N, typename T, int W, int COUNT, bool LARGE, int WS>
 __device__ __forceinline__ void trace_lds_init(const T* __restrict__ frag, T* sFrag, T* sWave) {
   using P = TraceOrder<N, T, LARGE>;
   copy_to_lds<COUNT, W>(frag, sFrag);
-  zero_pads<N, T>(sWave + (threadIdx.x >> 6) * P::WAVE_SZ, P::G * 48, threadIdx.x & 63);
+  zero_pads<N, T>(sWave + (threadIdx.x >> 6) * WS, P::G * 48, threadIdx.x & 63);
   __syncthreads();
 }
 
@@ -661,21 +671,89 @@ __device__ __forceinline__ void trace_tile(const DeviceTables& t, const KernelPh
   write_traces<N, T, PERT, LARGE>(fc, fl, sU, sGeo, sU + P::U_SZ, sFrag, lane, conn, nel, e0, tr);
 }
 
+// The viscous normal flux and the norm at node (f, j) of element k, whose state
+// is u ([4][Np]), on the lane itself, in the operations of write_traces: the
+// gradient is the matrix cores' chain of fused multiply-adds over the element's
+// nodes.  WALL: with the wall's ghost; else the element's own side alone.
+template <int N, typename T, bool PERT, bool WALL>
+__device__ __forceinline__ T node_trace(const DeviceTables& t, const KernelPhysics& ph, const FaceConst<T>& fc,
+                                        const double* u, int64_t k, int f, int j, T vn[4]) {
+  using P = TraceOrder<N, T>;
+  using O = Order<N, T>;
+  const T* frag = frag_table<T>(t);
+  const int n = face_node<N>(f, j);
+  T ur[4] = {T(0), T(0), T(0), T(0)}, us[4] = {T(0), T(0), T(0), T(0)};
+  const int at = ((n >> 4) * P::KS) * 64 + (n & 15);
+#pragma unroll 8
+  for (int m = 0; m < P::Np; ++m) {
+    const int fi = at + (m >> 2) * 64 + (m & 3) * 16;
+    const T dr = frag[fi], ds = frag[O::FD + fi];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const T v = (T)(u[c * P::Np + m] - (PERT ? ph.U_inf[c] : 0.0));
+      ur[c] += dr * v;
+      us[c] += ds * v;
+    }
+  }
+  const double* g = t.geo + k * kGeoStride;
+  const T rx = (T)g[0], ry = (T)g[1], sx = (T)g[2], sy = (T)g[3];
+  const T nx = (T)g[4 + 4 * f], ny = (T)g[5 + 4 * f];
+  T gx[4], gy[4], up[4], upf[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    gx[c] = rx * ur[c] + sx * us[c];
+    gy[c] = ry * ur[c] + sy * us[c];
+    up[c] = (T)(u[c * P::Np + n] - (PERT ? ph.U_inf[c] : 0.0));
+  }
+  full_state<T, PERT>(up, fc.base, upf);
+  const VState<T> sp = vstate(fc.gas, upf);
+  VState<T> so = sp;
+  if constexpr (WALL) {
+    T uo[4], uof[4];
+    ghost_state<T, PERT>(1, up, upf, nullptr, 0, fc.vwx, fc.vwy, fc.gas, fc.base, uo);
+    full_state<T, PERT>(uo, fc.base, uof);
+    so = vstate(fc.gas, uof);
+  }
+  T nrm = T(0);
+#pragma nounroll
+  for (int side = 0; side < (WALL ? 2 : 1); ++side) {
+    const T a1 = normal_diffusion_norm(fc.gas, side == 0 ? sp : so, nx, ny);
+    nrm = a1 > nrm ? a1 : nrm;
+  }
+  if constexpr (WALL)
+    viscous_normal_flux(gas_wall(fc.gas, fc.k_wall), so, gx, gy, nx, ny, vn);
+  else
+    viscous_normal_flux(fc.gas, sp, gx, gy, nx, ny, vn);
+  return nrm;
+}
+
+// Node (f, j)'s trace into place, with the largest of its face's norms, which lie
+// in `norms` by lane.
+template <int N, typename T>
+__device__ __forceinline__ void store_node_trace(typename Vec4<T>::type* __restrict__ tr, int64_t k, int f, int j,
+                                                 const T vn[4], const T* norms, int lane) {
+  using P = TraceOrder<N, T>;
+  T gmax = T(0);
+#pragma unroll
+  for (int jj = 0; jj < P::Nfp; ++jj) {
+    const T v = norms[lane - j + jj];
+    gmax = v > gmax ? v : gmax;
+  }
+  tr[k * P::NF + f * P::Nfp + j] = typename Vec4<T>::type{vn[1], vn[2], vn[3], gmax};
+}
+
 // The traces of the wall faces alone, for a wall velocity other than the one
 // they were written with: one lane per face node of the faces blk * F ..., F =
-// 64 / (p + 1), of the wall face list.  The gradient is the matrix cores' chain
-// of fused multiply-adds over the element's nodes.  norms: 64 values of LDS.
+// 64 / (p + 1), of the wall face list.  norms: 64 values of LDS.
 template <int N, typename T, bool PERT>
 __device__ __forceinline__ void wall_traces(const DeviceTables& t, const KernelPhysics& ph,
                                             const double* __restrict__ U,
                                             typename Vec4<T>::type* __restrict__ tr, int blk, T* norms) {
   using P = TraceOrder<N, T>;
-  using O = Order<N, T>;
   const int lane = threadIdx.x & 63;
   const int wf = blk * (64 / P::Nfp) + lane / P::Nfp, j = lane % P::Nfp;
   const bool ok = lane < 64 / P::Nfp * P::Nfp && wf < t.nwall;
   const FaceConst<T> fc = face_const<T>(ph);
-  const T* frag = frag_table<T>(t);
   T vn[4] = {T(0), T(0), T(0), T(0)};
   int64_t k = 0;
   int f = 0;
@@ -683,54 +761,33 @@ __device__ __forceinline__ void wall_traces(const DeviceTables& t, const KernelP
     const int kf = t.wall[wf];
     k = kf / 3;
     f = kf % 3;
-    const int n = face_node<N>(f, j);
-    const double* u = U + k * P::S;
-    T ur[4] = {T(0), T(0), T(0), T(0)}, us[4] = {T(0), T(0), T(0), T(0)};
-    const int at = ((n >> 4) * P::KS) * 64 + (n & 15);
-#pragma unroll 8
-    for (int m = 0; m < P::Np; ++m) {
-      const int fi = at + (m >> 2) * 64 + (m & 3) * 16;
-      const T dr = frag[fi], ds = frag[O::FD + fi];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const T v = (T)(u[c * P::Np + m] - (PERT ? ph.U_inf[c] : 0.0));
-        ur[c] += dr * v;
-        us[c] += ds * v;
-      }
-    }
-    const double* g = t.geo + k * kGeoStride;
-    const T rx = (T)g[0], ry = (T)g[1], sx = (T)g[2], sy = (T)g[3];
-    const T nx = (T)g[4 + 4 * f], ny = (T)g[5 + 4 * f];
-    T gx[4], gy[4], up[4], upf[4], uo[4], uof[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      gx[c] = rx * ur[c] + sx * us[c];
-      gy[c] = ry * ur[c] + sy * us[c];
-      up[c] = (T)(u[c * P::Np + n] - (PERT ? ph.U_inf[c] : 0.0));
-    }
-    full_state<T, PERT>(up, fc.base, upf);
-    ghost_state<T, PERT>(1, up, upf, nullptr, 0, fc.vwx, fc.vwy, fc.gas, fc.base, uo);
-    full_state<T, PERT>(uo, fc.base, uof);
-    const VState<T> sp = vstate(fc.gas, upf), so = vstate(fc.gas, uof);
-    T nrm = T(0);
-#pragma nounroll
-    for (int side = 0; side < 2; ++side) {
-      const T a1 = normal_diffusion_norm(fc.gas, side == 0 ? sp : so, nx, ny);
-      nrm = a1 > nrm ? a1 : nrm;
-    }
-    viscous_normal_flux(gas_wall(fc.gas, fc.k_wall), so, gx, gy, nx, ny, vn);
-    norms[lane] = nrm;
+    norms[lane] = node_trace<N, T, PERT, true>(t, ph, fc, U + k * P::S, k, f, j, vn);
   }
   wave_sync();
-  if (ok) {
-    T gmax = T(0);
-#pragma unroll
-    for (int jj = 0; jj < P::Nfp; ++jj) {
-      const T v = norms[lane - j + jj];
-      gmax = v > gmax ? v : gmax;
-    }
-    tr[k * P::NF + f * P::Nfp + j] = typename Vec4<T>::type{vn[1], vn[2], vn[3], gmax};
+  if (ok) store_node_trace<N, T>(tr, k, f, j, vn, norms, lane);
+}
+
+// The traces of one element of the curved set towards its straight neighbours,
+// from its state u (in LDS, synced).  The set holds the isoparametric elements'
+// face neighbours too, so those neighbours face an affine element: its traces are
+// those of any straight one.  Nobody reads the set's other traces.  norms: 64
+// values of LDS.
+template <int N, typename T, bool PERT>
+__device__ __forceinline__ void element_traces(const DeviceTables& t, const KernelPhysics& ph, const double* u,
+                                               int64_t k, typename Vec4<T>::type* __restrict__ tr, T* norms) {
+  using P = TraceOrder<N, T>;
+  const int lane = threadIdx.x & 63;
+  const int f = lane / P::Nfp, j = lane % P::Nfp;
+  bool ok = false;
+  if (lane < P::NF) {
+    const int conn = t.conn[k * 3 + f];
+    ok = (conn & 3) == 0 && t.cslot[conn >> 4] < 0;
   }
+  const FaceConst<T> fc = face_const<T>(ph);
+  T vn[4] = {T(0), T(0), T(0), T(0)};
+  if (ok) norms[lane] = node_trace<N, T, PERT, false>(t, ph, fc, u, k, f, j, vn);
+  wave_sync();
+  if (ok) store_node_trace<N, T>(tr, k, f, j, vn, norms, lane);
 }
 
 namespace {
