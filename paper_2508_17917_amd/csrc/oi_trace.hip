@@ -14,11 +14,11 @@
 // CU's 160 KB); at p >= 5 (88 and 151 KB) they are read from the L2 as before.
 //
 // us a stage on 20,480 elements, that stage -> this: p = 1 21.5 -> 15.4, p = 2
-// 25.7 -> 21.6, p = 3 45.6 -> 27.1, p = 4 89.4 -> 57.6, p = 5 186.6 -> 113.2, p = 6
+// 25.7 -> 21.6, p = 3 45.6 -> 27.1, p = 4 89.4 -> 54.2, p = 5 186.6 -> 113.2, p = 6
 // 404 -> 346.  Bound by the FP64 units, which the matrix and the vector
-// instructions share: at p = 4 98 matrix instructions of 64 cycles (half of
-// their rows, columns and depth padding: 3 of 4 element slots, 49 of 64 points)
-// and about 1,300 vector instructions of 4 a tile, 6.7 tiles a SIMD.
+// instructions share: at p = 4 84 matrix instructions of 64 cycles (a quarter of
+// their rows idle: three of four element slots) and about 1,200 vector
+// instructions of 4 a tile, 6.7 tiles a SIMD.
 #include <hip/hip_runtime.h>
 
 #include "trace_device.h"
@@ -40,6 +40,10 @@ struct OITrace {
       P::U_SZ + P::F_SZ > H_OFF + P::H_SZ ? P::U_SZ + P::F_SZ : H_OFF + P::H_SZ;
   static constexpr int WAVE_SZ = (AREA + P::EPT * kGeoStride + 3) / 4 * 4;
   static constexpr int NQ = (P::EPT * P::S + 63) / 64;
+  // one point beyond whole chunks (p = 4: 49) and a free element slot: no chunk of
+  // its own
+  static constexpr bool TAIL = P::Nq % 16 == 1 && P::EPT < 4 && 12 * P::EPT <= 64;
+  static constexpr int CHUNKS = TAIL ? P::NQT - 1 : P::NQT;
   static constexpr int TAB = LDS_FRAG ? P::TOTAL : P::LDS_TAB;  // shared LDS (doubles)
   static constexpr int OFF_TAB = LDS_FRAG ? P::OFF_DRSF : 0;    // face-point tables in it
   static constexpr int FIRST = LDS_FRAG ? 0 : P::OFF_DRSF;      // its first value in the packed array
@@ -229,12 +233,30 @@ __device__ __forceinline__ void oi_trace_tiles(const DeviceTables& t, const Kern
     if constexpr (!Q::LATE) load_traces();
     wave_sync();
 
-    // ---- element points, chunk by chunk; the divergence accumulates in acc
+    // ---- element points, chunk by chunk; the divergence accumulates in acc.
+    // TAIL: the last point's 12 values per element (U, d_r U, d_s U) are dot
+    // products, one a lane, in the order of the matrix cores' chain; the free
+    // slot's lanes form its flux with the first chunk's, and its share of the
+    // divergence follows the other points' on the vector unit.  p = 4, 20,480
+    // elements: 57.3 us a stage with a chunk for the one point, 54.2 without.
+    if constexpr (Q::TAIL) {
+      const int op = lane / (4 * EPT), r = lane - op * (4 * EPT), c = r / EPT, e = r - c * EPT;
+      if (op < 3) {
+        const double* fr = G + (op == 0 ? P::OFF_IQ : (op == 1 ? P::OFF_DRQ : P::OFF_DSQ)) + (NQT - 1) * KS * 64;
+        const double* u = sU + (ROWC * c + ROWE * e) * RS;
+        double v = 0.0;
+#pragma unroll
+        for (int k = 0; k < Np; ++k) v = __builtin_fma(u[k], fr[(k >> 2) * 64 + (k & 3) * 16], v);
+        sF[lane] = v;
+      }
+      wave_sync();
+    }
+    double tFr[4] = {0.0, 0.0, 0.0, 0.0}, tFs[4] = {0.0, 0.0, 0.0, 0.0};
     V4 acc[NT];
 #pragma unroll
     for (int tt = 0; tt < NT; ++tt) acc[tt] = V4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
-    for (int tq = 0; tq < NQT; ++tq) {
+    for (int tq = 0; tq < Q::CHUNKS; ++tq) {
       V4 aU = {0.0, 0.0, 0.0, 0.0}, aR = aU, aS = aU;
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
@@ -245,8 +267,17 @@ __device__ __forceinline__ void oi_trace_tiles(const DeviceTables& t, const Kern
         aS = mfma(av, G[P::OFF_DSQ + fo], aS);
       }
       double Fr[4] = {0.0, 0.0, 0.0, 0.0}, Fs[4] = {0.0, 0.0, 0.0, 0.0};
-      if (re < nel && 16 * tq + rn < Nq) {
-        const double* g = sGeo + re * kGeoStride;
+      const bool tail = Q::TAIL && tq == 0 && re == EPT && rn < nel;
+      if (tail) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          aU[c] = sF[c * EPT + rn];
+          aR[c] = sF[(4 + c) * EPT + rn];
+          aS[c] = sF[(8 + c) * EPT + rn];
+        }
+      }
+      if (tail || (re < nel && 16 * tq + rn < Nq)) {
+        const double* g = sGeo + (tail ? rn : re) * kGeoStride;
         const double rx = g[0], ry = g[1], sx = g[2], sy = g[3];
         double u[4], gx[4], gy[4];
 #pragma unroll
@@ -265,6 +296,14 @@ __device__ __forceinline__ void oi_trace_tiles(const DeviceTables& t, const Kern
           const double fx = Fx[c] - fvx[c], fy = Fy[c] - fvy[c];
           Fr[c] = rx * fx + ry * fy;
           Fs[c] = sx * fx + sy * fy;
+        }
+      }
+      if constexpr (Q::TAIL) {
+        wave_sync();
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          tFr[c] = tq == 0 ? Fr[c] : tFr[c];
+          tFs[c] = tq == 0 ? Fs[c] : tFs[c];
         }
       }
 #pragma unroll
@@ -289,6 +328,23 @@ __device__ __forceinline__ void oi_trace_tiles(const DeviceTables& t, const Kern
       wave_sync();
     }
 
+    if constexpr (Q::TAIL) {
+      const int src = 16 * EPT + (re < EPT ? re : 0);
+      double wr[NT], ws[NT];
+#pragma unroll
+      for (int tt = 0; tt < NT; ++tt) {
+        const int fo = (tt * KQ + KQ - 1) * 64 + rn;
+        wr[tt] = G[P::OFF_WR + fo];
+        ws[tt] = G[P::OFF_WS + fo];
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const double fr = lane_read(tFr[c], src), fs = lane_read(tFs[c], src);
+#pragma unroll
+        for (int tt = 0; tt < NT; ++tt)
+          acc[tt][c] = __builtin_fma(fs, ws[tt], __builtin_fma(fr, wr[tt], acc[tt][c]));
+      }
+    }
     if constexpr (Q::LATE) load_traces();
     // ---- K1 (and at p = 6 K0) of the tile's outputs, covered by the face pass
     double rk[NT][4], r0[NT][4];
