@@ -303,21 +303,20 @@ def curved_bytes_per_element(Np, Nfp):
 
 
 def stage_time(s, U, dt, stream, nl=100):
-    """Average duration of the stage kernel alone (HIP events on its stream),
-    on scratch copies so the caller's state is left alone."""
+    """Average duration of a stage launch as the timed steps run it (HIP events
+    on the stream around one multi-step call of nl stages without forces, the
+    launch that makes its first face traces included), on scratch copies so the
+    caller's state is left alone."""
     import torch
-    Ua, Ub = U.clone(), torch.empty_like(U)
-    Kb = torch.zeros_like(U)
-    for _ in range(5):
-        s.rk_stage(Ua, Ub, Kb, -0.4, 0.3, dt, stream=stream)
+    Ua, Kb = U.clone(), torch.zeros_like(U)
+    s.rk_steps(Ua, Kb, 2, dt, stream=stream)
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
     e0.record(stream)
-    for _ in range(nl):
-        s.rk_stage(Ua, Ub, Kb, -0.4, 0.3, dt, stream=stream)
+    s.rk_steps(Ua, Kb, nl // 5, dt, stream=stream)
     e1.record(stream)
     torch.cuda.synchronize()
-    return e0.elapsed_time(e1) / 1e3 / nl
+    return e0.elapsed_time(e1) / 1e3 / (nl // 5 * 5)
 
 
 def settle(s, U, dt, stream, ms=50.0, max_launches=4000):
@@ -820,8 +819,8 @@ def measure(wname, p, form, steps, warmup, overint=False, compare_forms=False, c
                            "l2_rel_err": rel_l2([s64], [Uf], [U64], w["U_inf"])}
             sf.close()
         config["other_forms"] = forms
-    kernel = ("oi_stage_kernel<%d> (over-integrated, fp64)" % p if overint
-              else "stage_kernel<%d, %s>" % (p, form))
+    kernel = ("oi_trace_stage_kernel<%d> (over-integrated, fp64)" % p if overint
+              else "%sstage_kernel<%d, %s>" % ("" if form == "bf16-ops" else "trace_", p, form))
     traffic = None if overint else measured_traffic(wname, p, form)
     roof = roofline(Np, p + 1, K, t_launch, "fp64" if overint else form, traffic, overint)
     roof["kernel"] = kernel
@@ -917,8 +916,8 @@ def viv_report(args, prec):
                               ", ".join(desc), sum(s.K for s in solvers64), args.form),
               "instances": len(cases), "dofs": dofs, "form": args.form,
               "launch_shape": shape, "dt": [float(x) for x in dts], "finite": finite}
-    kernel = ("batch_stage_kernel<%s>" if shape.startswith("one launch per stage")
-              else "batch_order_kernel<p, %s> (one launch per order)") % args.form
+    kernel = ("batch_trace_stage_kernel<%s>" if shape.startswith("one launch per stage")
+              else "batch_trace_order_kernel<p, %s> (one launch per order)") % args.form
     mdt = MFMA_DTYPE[args.form]
     t = {"hbm": nbytes / (HBM_PEAK_GBS * 1e9), "mfma": gemm / (MFMA_PEAK_TFLOPS[mdt] * 1e12),
          "alu": pw / (VALU_PEAK_TFLOPS * 1e12)}
