@@ -68,7 +68,7 @@ struct TraceOrder {
   static constexpr int AREA = U_SZ + F_SZ > H_OFF + H_SZ ? U_SZ + F_SZ : H_OFF + H_SZ;
   static constexpr int WAVE_SZ = (AREA + EPT * kGeoStride + 3) / 4 * 4;
   static_assert(!FLAT || G * 16 * RS <= H_SZ, "the residual rows take the face terms' area");
-  static constexpr int PAD = RS - Np;
+  static constexpr int PAD = 4 * KS - Np;  // pad columns that the products over the nodes read
   static constexpr int WAVES = 4;
   // registers: three waves per SIMD in FP32, two in FP64 (four and three spill:
   // p = 4 FP32 16.4 -> 18.1 us, FP64 22.6 -> 24.6).  K1 / K0 are loaded before the
@@ -198,15 +198,17 @@ __device__ __forceinline__ void fetch_gradient(const T (&gxk)[TraceOrder<N, T, L
     }
 }
 
-// Zero the pad columns of `rows` rows of RS values (the matrix-core products
-// read them against zero operator entries, so they must hold finite values).
+// Zero the pad columns of `rows` rows of RS values.  The matrix-core products
+// read them against zero operator entries, and 0 times a NaN or an infinity is
+// not 0: a row is one element's, its pads must be no other's.
 template <int N, typename T>
 __device__ __forceinline__ void zero_pads(T* rows0, int rows, int lane) {
   using P = TraceOrder<N, T>;
-  for (int i = lane; i < rows * P::PAD; i += 64) {
-    const int r = i / P::PAD;
-    rows0[r * P::RS + P::Np + (i - r * P::PAD)] = T(0);
-  }
+  if constexpr (P::PAD > 0)
+    for (int i = lane; i < rows * P::PAD; i += 64) {
+      const int r = i / P::PAD;
+      rows0[r * P::RS + P::Np + (i - r * P::PAD)] = T(0);
+    }
 }
 
 // The traces of the states staged in sU (synced): one lane per face node of
@@ -364,7 +366,9 @@ __device__ __forceinline__ void trace_tiles(const DeviceTables& t, const KernelP
 #pragma unroll
     for (int q = 0; q < NG; ++q)
       if (lane + 64 * q < nel * kGeoStride) sGeo[lane + 64 * q] = (T)rg[q];
-    if constexpr (P::OVER) zero_pads<N, T>(sU, G * 48, lane);
+    // the last tile's face terms and norms lay on the flux rows (OVER: on the state
+    // rows too)
+    zero_pads<N, T>(P::OVER ? sU : sFr, P::OVER ? G * 48 : G * 32, lane);
     // the face node's other side: its state (4 strided values) and its trace;
     // a boundary face points at the element itself
     const bool okf = lane < nel * NF;
@@ -374,7 +378,7 @@ __device__ __forceinline__ void trace_tiles(const DeviceTables& t, const KernelP
     auto kept = [&](int e) { return !CURVED || !((skip >> e) & 1); };
     const int conn = __builtin_amdgcn_ds_bpermute((fl.e * 3 + fl.f) << 2, rc);
     const int tag = conn & 3;
-    V4 own = rt;
+    const V4 own = rt;
     double un[4];
     V4 nbt;
     {
@@ -387,10 +391,8 @@ __device__ __forceinline__ void trace_tiles(const DeviceTables& t, const KernelP
       for (int c = 0; c < 4; ++c) un[c] = up[c * Np];
       nbt = tr_in[ne * NF + mfo * Nfp + mj];
     }
-    // between elements of the set no traces are written: what those lanes read may
-    // be anything, and what they make must stay finite (the next tile's products
-    // read some of it against zeros)
-    if (!kept(fl.e)) own = nbt = V4{T(0), T(0), T(0), T(0)};
+    // (between elements of the set no traces are written: what those lanes read may
+    // be anything, and stays in those elements' rows)
     wave_sync();
 
     // ---- gradient on the matrix cores, volume flux per node, contravariant
