@@ -214,7 +214,7 @@ __device__ __forceinline__ void zero_pads(T* rows0, int rows, int lane) {
 // The traces of the states staged in sU (synced): one lane per face node of
 // the tile's nel elements.  Boundary faces carry the wall's or the far field's
 // viscous flux, and the ghost's norm in the maximum.  skip: the slots (bits) whose
-// traces another wave writes.
+// traces another wave writes; their new states are not in sU.
 template <int N, typename T, bool PERT, bool LARGE>
 __device__ __forceinline__ void write_traces(const FaceConst<T>& fc, const FaceLane<N, T, LARGE>& fl,
                                              const T* sU, const T* sGeo, T* sNorm, const T* sFrag,
@@ -225,7 +225,7 @@ __device__ __forceinline__ void write_traces(const FaceConst<T>& fc, const FaceL
   tile_gradient<N, T, LARGE>(sU, sGeo, sFrag, lane, nel, gxk, gyk);
   T gxp[4], gyp[4];
   fetch_gradient<N, T, LARGE>(gxk, gyk, fl.e, fl.n, gxp, gyp);
-  const bool ok = lane < nel * P::NF;
+  const bool ok = lane < nel * P::NF && !((skip >> fl.e) & 1);
   T vn[4] = {T(0), T(0), T(0), T(0)};
   T nrm = T(0);
   if (ok) {
@@ -258,7 +258,7 @@ __device__ __forceinline__ void write_traces(const FaceConst<T>& fc, const FaceL
     sNorm[lane] = nrm;
   }
   wave_sync();
-  if (ok && !((skip >> fl.e) & 1)) {
+  if (ok) {
     T gmax = T(0);
 #pragma unroll
     for (int jj = 0; jj < P::Nfp; ++jj) {
@@ -602,7 +602,7 @@ __device__ __forceinline__ void trace_tiles(const DeviceTables& t, const KernelP
       for (int i = 0; i < NO; ++i) {
         const int at = P::FLAT ? lds_u[P::FLAT ? i : 0] : row_of<N, T, LARGE>(i, re) * RS + rn;
         const bool in = P::FLAT ? lane + 64 * i < nel * S : (re < nel && rn < Np);
-        if (in) sU[at] = (T)(unew[i] - uinf(P::FLAT ? field[P::FLAT ? i : 0] : i));
+        if (in && kept(P::FLAT ? (lane + 64 * i) / S : re)) sU[at] = (T)(unew[i] - uinf(P::FLAT ? field[P::FLAT ? i : 0] : i));
       }
       if constexpr (P::OVER) zero_pads<N, T>(sU, G * 16, lane);
       wave_sync();

@@ -12,6 +12,7 @@ import numpy as np
 import pytest
 
 import meshgen as mg
+from tests.test_gpu_curved_traces import _curved_solver
 from tests.test_gpu_traces import _batch_case, _chain, _solver, _state, _torch
 
 pytestmark = pytest.mark.gpu
@@ -57,6 +58,24 @@ def test_a_bad_element_stays_within_the_stencil(p, precision, kind):
     # (the over-integrated points are not the nodes: there the tiny density is none)
     _steps_against_chain(torch, s, _state(torch, s, p), [(s.K // 2 + 1, kind)], [(4, 3), (2, 3), (4, 0)],
                          spreads=not (precision == "overint" and kind == "tiny"))
+    s.close()
+
+
+@pytest.mark.parametrize("kind", ["nan", "inf"])
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("p", range(1, 7))
+def test_a_bad_element_of_the_curved_set(p, precision, kind):
+    """The bad element in the set that other waves advance (the first wall
+    element, and a face neighbour of another): the straight tiles leave its
+    outputs and traces out, and nothing of it reaches the elements after it.
+    The chain is compared on the elements that stay finite as well as by where
+    they do."""
+    torch = _torch()
+    print("[gpu-case] non-finite curved %s p=%d precision=%d" % (kind, p, precision), flush=True)
+    s = _curved_solver(67, 64, 1.02, p, precision, 1.0)
+    curved = np.flatnonzero(s.table("curved_slot") >= 0)
+    bad = [(int(curved[0]), kind), (int(curved[-1]), kind)]
+    _steps_against_chain(torch, s, _state(torch, s, p), bad, [(4, 3), (2, 3), (4, 0)])
     s.close()
 
 
