@@ -347,14 +347,16 @@ static int batch_build(dg_batch* b, dg_ctx* const* ctxs, int n) {
   b->A.assign(n, nullptr);
   b->B.assign(n, nullptr);
   b->K1.assign(n, nullptr);
-  // face traces (bfloat16 operators have none), where the step's extra launch
+  // face traces, where they serve every instance, the step's extra launch
   // pays and the memory for them is there
   int64_t elements = 0, bytes = 0;
+  bool served = b->form <= 2;
   for (int i = 0; i < n; ++i) {
+    served = served && dgmi::ctx_trace_bytes(ctxs[i]) > 0;
     elements += ctxs[i]->K;
     bytes += dgmi::trace_stage_bytes(ctxs[i]->N, b->form, ctxs[i]->K);
   }
-  if (b->form <= 2 && elements >= 16384) {
+  if (served && elements >= 16384) {
     b->tr.assign(2 * n, nullptr);
     for (int i = 0; i < 2 * n; ++i)
       if (hipMalloc(&b->tr[i], dgmi::trace_bytes(ctxs[i / 2]->N, b->form, ctxs[i / 2]->K)) != hipSuccess) {

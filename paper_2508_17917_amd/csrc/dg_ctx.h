@@ -122,10 +122,14 @@ struct StateBuffers {
 constexpr size_t kSecondScratch = (size_t)64 << 20;
 // Face traces serve every form but bfloat16 operators, and meshes with curved
 // elements where the stage's arrays fit the last-level cache (beyond it the
-// stages run from the neighbours' states).  Over-integration switched on after
-// the set-up finds arrays of the nodal size and runs without them.
+// stages run from the neighbours' states).  A side takes the other's normal flux
+// with the sign changed, so they do not serve a mesh with a periodic seam whose
+// sides have other normals (vertices that are not exact translates).
+// Over-integration switched on after the set-up finds arrays of the nodal size
+// and runs without them.
 inline size_t ctx_trace_bytes(const dg_ctx* c) {
   const int form = ctx_form(c);
+  if (!c->mesh.opposed) return 0;
   if (!c->mesh.celem.empty() && (form == kFormOverint || beyond_cache(trace_stage_bytes(c->N, form, c->K)))) return 0;
   return trace_bytes(c->N, form, c->K);
 }

@@ -71,6 +71,7 @@ struct MeshTables {
   std::vector<int32_t> nbr_face;  // K x 3
   std::vector<int8_t> tag;        // K x 3
   std::vector<double> x, y;       // K x Np node coordinates
+  bool opposed = true;            // both sides' normals of every interior face negate each other exactly
   std::vector<int32_t> wall_faces;  // list of k*3+f with tag wall
   std::vector<double> wall_xy;      // (x, y) of each wall face node, face-major
   // isoparametric elements (curved_setup.cpp): the set S of the curved

@@ -506,6 +506,7 @@ bool build_mesh_tables(const RefOps& ref, const Physics& ph, int64_t Nv, const d
     keys[kf] = {(int64_t)std::llround(wx / tol), (int64_t)std::llround(wy / tol)};
     table[keys[kf]].push_back(kf);
   }
+  t.opposed = true;
   for (int64_t kf = 0; kf < K * 3; ++kf) {
     int64_t k = kf / 3;
     int f = int(kf % 3);
@@ -552,12 +553,12 @@ bool build_mesh_tables(const RefOps& ref, const Physics& ph, int64_t Nv, const d
     }
     t.nbr[kf] = (int32_t)kn;
     t.nbr_face[kf] = fn;
-    // the two sides' normals negate each other exactly (shared vertices give
-    // that; across a periodic seam the edge vectors may round apart), so that
-    // a side can take the other's normal flux with the sign changed
-    if (cand[0] > kf)
-      for (int c = 0; c < 2; ++c)
-        t.geo[kn * kGeoStride + 4 + 4 * fn + c] = -t.geo[k * kGeoStride + 4 + 4 * f + c];
+    // shared vertices give normals that negate each other exactly; across a
+    // periodic seam the edge vectors may differ, by rounding up to the matching
+    // tolerance
+    for (int c = 0; c < 2; ++c)
+      if (t.geo[kn * kGeoStride + 4 + 4 * fn + c] != -t.geo[k * kGeoStride + 4 + 4 * f + c])
+        t.opposed = false;
   }
   // penalty geometric factor per face (sigma_e = sigma_geo * Gbar_e)
   for (int64_t k = 0; k < K; ++k) {
