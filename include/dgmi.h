@@ -316,7 +316,9 @@ typedef struct dg_batch dg_batch;
 
 /* Create a batch of the n contexts ctxs[0..n-1] (all set up by dg_setup,
  * each at most once: DG_EINVAL for a repeated context).  Allocates device
- * memory (3 states per instance) and pinned host memory. */
+ * memory (3 states per instance, without which DG_ENOMEM; then, where its steps
+ * use face traces and these leave half of the free memory, 24 (p + 1) values per
+ * element) and pinned host memory. */
 int dg_batch_create(dg_ctx* const* ctxs, int n, dg_batch** out);
 
 /* Copy instance i's state in from / out to a device array [K_i][4][Np_i]

@@ -347,16 +347,43 @@ static int batch_build(dg_batch* b, dg_ctx* const* ctxs, int n) {
   b->A.assign(n, nullptr);
   b->B.assign(n, nullptr);
   b->K1.assign(n, nullptr);
-  // face traces, where they serve every instance, the step's extra launch
-  // pays and the memory for them is there
-  int64_t elements = 0, bytes = 0;
+  for (int i = 0; i < n; ++i) {
+    const size_t bytes = state_bytes(ctxs[i]);
+    if ((e = hipMalloc((void**)&b->A[i], bytes)) != hipSuccess ||
+        (e = hipMalloc((void**)&b->B[i], bytes)) != hipSuccess ||
+        (e = hipMalloc((void**)&b->K1[i], bytes)) != hipSuccess ||
+        (e = hipMemset(b->A[i], 0, bytes)) != hipSuccess ||
+        (e = hipMemset(b->B[i], 0, bytes)) != hipSuccess ||
+        (e = hipMemset(b->K1[i], 0, bytes)) != hipSuccess)
+      return e == hipErrorOutOfMemory ? bfail(b, DG_ENOMEM, "device allocation failed")
+                                      : bhip(b, e, "allocating batch states");
+  }
+  if ((e = hipMalloc((void**)&b->d_items, n * sizeof(dgmi::BatchItem))) != hipSuccess ||
+      (e = hipMalloc((void**)&b->d_steps, n * sizeof(dgmi::BatchStep))) != hipSuccess ||
+      (e = hipMemset(b->d_steps, 0, n * sizeof(dgmi::BatchStep))) != hipSuccess ||
+      (e = hipMalloc((void**)&b->d_parity, sizeof(int))) != hipSuccess ||
+      (e = hipMemset(b->d_parity, 0, sizeof(int))) != hipSuccess ||
+      (e = hipHostMalloc((void**)&b->h_steps, n * sizeof(dgmi::BatchStep))) != hipSuccess ||
+      (e = hipHostMalloc((void**)&b->h_parity, sizeof(int))) != hipSuccess ||
+      (e = hipHostMalloc((void**)&b->h_force, 4 * n * sizeof(double))) != hipSuccess ||
+      (e = hipMalloc((void**)&b->d_fitems, n * sizeof(dgmi::ForceItem))) != hipSuccess ||
+      (e = hipHostMalloc((void**)&b->h_fitems, n * sizeof(dgmi::ForceItem))) != hipSuccess ||
+      (e = hipHostMalloc((void**)&b->h_items, n * sizeof(dgmi::BatchItem))) != hipSuccess ||
+      (e = hipEventCreateWithFlags(&b->upload_ev, hipEventDisableTiming)) != hipSuccess ||
+      (e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking)) != hipSuccess)
+    return bhip(b, e, "allocating batch tables");
+  // face traces last, the batch runs without them: where they serve every
+  // instance, the step's extra launch pays and they leave half of what is free
+  int64_t elements = 0, stage = 0;
+  size_t traces = 0;
   bool served = b->form <= 2;
   for (int i = 0; i < n; ++i) {
-    served = served && dgmi::ctx_trace_bytes(ctxs[i]) > 0;
     elements += ctxs[i]->K;
-    bytes += dgmi::trace_stage_bytes(ctxs[i]->N, b->form, ctxs[i]->K);
+    stage += dgmi::trace_stage_bytes(ctxs[i]->N, b->form, ctxs[i]->K);
+    traces += 2 * dgmi::trace_bytes(ctxs[i]->N, b->form, ctxs[i]->K);
+    served = served && dgmi::ctx_trace_bytes(ctxs[i]) > 0;
   }
-  if (served && elements >= 16384) {
+  if (served && elements >= 16384 && dgmi::leaves_half(traces)) {
     b->tr.assign(2 * n, nullptr);
     for (int i = 0; i < 2 * n; ++i)
       if (hipMalloc(&b->tr[i], dgmi::trace_bytes(ctxs[i / 2]->N, b->form, ctxs[i / 2]->K)) != hipSuccess) {
@@ -366,21 +393,12 @@ static int batch_build(dg_batch* b, dg_ctx* const* ctxs, int n) {
         (void)hipGetLastError();
         break;
       }
-    b->large = dgmi::beyond_cache(bytes);
+    b->large = dgmi::beyond_cache(stage);
   }
   for (int j = 0; j < n; ++j) {
     const int i = idx[j];
     dg_ctx* c = ctxs[i];
     b->item_of[i] = j;
-    const size_t bytes = state_bytes(c);
-    if ((e = hipMalloc((void**)&b->A[i], bytes)) != hipSuccess ||
-        (e = hipMalloc((void**)&b->B[i], bytes)) != hipSuccess ||
-        (e = hipMalloc((void**)&b->K1[i], bytes)) != hipSuccess ||
-        (e = hipMemset(b->A[i], 0, bytes)) != hipSuccess ||
-        (e = hipMemset(b->B[i], 0, bytes)) != hipSuccess ||
-        (e = hipMemset(b->K1[i], 0, bytes)) != hipSuccess)
-      return e == hipErrorOutOfMemory ? bfail(b, DG_ENOMEM, "device allocation failed")
-                                      : bhip(b, e, "allocating batch states");
     dgmi::BatchItem& it = items[j];
     it.t = dgmi::ctx_tables(c);
     it.ph = dgmi::ctx_phys(c, nullptr);
@@ -409,22 +427,8 @@ static int batch_build(dg_batch* b, dg_ctx* const* ctxs, int n) {
     g.n_items += 1;
   }
   if ((int)b->groups.size() > dgmi::kMaxOrder) return bfail(b, DG_EINVAL, "too many order groups");
-  if ((e = hipMalloc((void**)&b->d_items, n * sizeof(dgmi::BatchItem))) != hipSuccess ||
-      (e = hipMemcpy(b->d_items, items.data(), n * sizeof(dgmi::BatchItem),
-                     hipMemcpyHostToDevice)) != hipSuccess ||
-      (e = hipMalloc((void**)&b->d_steps, n * sizeof(dgmi::BatchStep))) != hipSuccess ||
-      (e = hipMemset(b->d_steps, 0, n * sizeof(dgmi::BatchStep))) != hipSuccess ||
-      (e = hipMalloc((void**)&b->d_parity, sizeof(int))) != hipSuccess ||
-      (e = hipMemset(b->d_parity, 0, sizeof(int))) != hipSuccess ||
-      (e = hipHostMalloc((void**)&b->h_steps, n * sizeof(dgmi::BatchStep))) != hipSuccess ||
-      (e = hipHostMalloc((void**)&b->h_parity, sizeof(int))) != hipSuccess ||
-      (e = hipHostMalloc((void**)&b->h_force, 4 * n * sizeof(double))) != hipSuccess ||
-      (e = hipMalloc((void**)&b->d_fitems, n * sizeof(dgmi::ForceItem))) != hipSuccess ||
-      (e = hipHostMalloc((void**)&b->h_fitems, n * sizeof(dgmi::ForceItem))) != hipSuccess ||
-      (e = hipHostMalloc((void**)&b->h_items, n * sizeof(dgmi::BatchItem))) != hipSuccess ||
-      (e = hipEventCreateWithFlags(&b->upload_ev, hipEventDisableTiming)) != hipSuccess ||
-      (e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking)) != hipSuccess)
-    return bhip(b, e, "allocating batch tables");
+  if ((e = hipMemcpy(b->d_items, items.data(), n * sizeof(dgmi::BatchItem), hipMemcpyHostToDevice)) != hipSuccess)
+    return bhip(b, e, "item upload");
   std::copy(items.begin(), items.end(), b->h_items);
   return plan(b);
 }

@@ -81,6 +81,12 @@ DeviceTables ctx_tables(const dg_ctx* c);
 // over-integrated FP64 stage)
 inline int ctx_form(const dg_ctx* c) { return c->overint ? kFormOverint : c->precision; }
 KernelPhysics ctx_phys(const dg_ctx* c, const double vw[2]);
+// Whether memory that a call can do without may be taken: at most half of what
+// is free on the current device, the rest for what a program cannot.
+inline bool leaves_half(size_t bytes) {
+  size_t room = 0, total = 0;
+  return hipMemGetInfo(&room, &total) == hipSuccess && bytes <= room / 2;
+}
 // The stages of one multi-step call: from face traces where the call has
 // buffers for them (tr), else from the neighbours' states.  begin() takes the
 // call's first state; the last stage of the call leaves no traces.

@@ -1,0 +1,146 @@
+"""Device memory of contexts and batches, counted on the CPU.
+
+A child process loads a stand-in for the HIP runtime's memory, stream and launch
+calls ahead of the library (device memory is host memory with a budget, kernels
+do nothing), so that set-up, batch creation and steps run without a GPU and an
+allocation past the budget fails as it would on one.
+"""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2508_17917_amd", "libdgmi.so")
+pytestmark = [pytest.mark.skipif(not os.path.exists(LIB), reason="libdgmi.so not built"),
+              pytest.mark.skipif(shutil.which("g++") is None, reason="no g++")]
+
+SHIM = r"""
+#include <cstdlib>
+#include <cstring>
+#include <map>
+static std::map<void*, size_t> blocks;
+static size_t used = 0, budget = (size_t)1 << 40;
+static int capturing = 0, launches = 0;
+extern "C" {
+size_t shim_used() { return used; }
+void shim_budget(size_t b) { budget = b; }
+void shim_capturing(int c) { capturing = c; }
+int hipMalloc(void** p, size_t n) {
+  if (capturing) return 900;
+  if (used + n > budget) return 2;
+  *p = malloc(n ? n : 1);
+  blocks[*p] = n;
+  used += n;
+  return 0;
+}
+int hipFree(void* p) {
+  auto it = blocks.find(p);
+  if (it == blocks.end()) return p ? 1 : 0;
+  used -= it->second;
+  blocks.erase(it);
+  free(p);
+  return 0;
+}
+int hipHostMalloc(void** p, size_t n, unsigned) { *p = malloc(n ? n : 1); return 0; }
+int hipHostFree(void* p) { free(p); return 0; }
+int hipMemGetInfo(size_t* f, size_t* t) { *f = budget > used ? budget - used : 0; *t = budget; return 0; }
+int hipMemcpy(void* d, const void* s, size_t n, int) { memcpy(d, s, n); return 0; }
+int hipMemcpyAsync(void* d, const void* s, size_t n, int, void*) { memcpy(d, s, n); return 0; }
+int hipMemset(void* d, int v, size_t n) { memset(d, v, n); return 0; }
+int hipMemsetAsync(void* d, int v, size_t n, void*) { memset(d, v, n); return 0; }
+int hipGetDevice(int* d) { *d = 0; return 0; }
+int hipGetLastError() { return 0; }
+int hipDeviceSynchronize() { return 0; }
+int hipGetSymbolAddress(void** p, const void*) { static double a[1 << 23]; *p = a; return 0; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 1; return 0; }
+int hipDeviceGetAttribute(int* v, int, int) { *v = 256; return 0; }
+int hipEventCreate(void** e) { *e = malloc(1); return 0; }
+int hipEventCreateWithFlags(void** e, unsigned) { *e = malloc(1); return 0; }
+int hipEventDestroy(void* e) { free(e); return 0; }
+int hipEventRecord(void*, void*) { return 0; }
+int hipEventSynchronize(void*) { return 0; }
+int hipStreamCreateWithFlags(void** s, unsigned) { *s = malloc(1); return 0; }
+int hipStreamDestroy(void* s) { free(s); return 0; }
+int hipStreamSynchronize(void*) { return 0; }
+int hipStreamIsCapturing(void*, int* c) { *c = capturing; return 0; }
+int hipThreadExchangeStreamCaptureMode(int*) { return 0; }
+int hipLaunchKernel(const void*, unsigned long, unsigned, unsigned long, unsigned, void**, size_t, void*) { ++launches; return 0; }
+int __hipPushCallConfiguration(unsigned long, unsigned, unsigned long, unsigned, size_t, void*) { return 0; }
+int __hipPopCallConfiguration(void*, void*, void*, void*) { return 0; }
+}
+"""
+
+PRELUDE = r"""
+import ctypes, sys
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+shim.shim_used.restype = ctypes.c_size_t
+shim.shim_budget.argtypes = [ctypes.c_size_t]
+sys.path.insert(0, sys.argv[2])
+import meshgen as mg
+from paper_2508_17917_amd import _lib as L
+lib = L.load()
+
+def context(p, nt, nr, precision=0, mesh=None):
+    m = mesh or mg.ogrid(nt, nr, 0.5, 5.0, 1.02)
+    h = L.dg_create(p, precision)
+    L.dg_set_physics(h, 1.4, 0.72, 1e-3, 1.0, 0, 1.0, [1, 0.2, 0, 1.8])
+    L.dg_set_mesh(h, m["VX"], m["VY"], m["EToV"], m["face_tag"], m["period"])
+    L.dg_setup(h)
+    return h
+
+def state(p, K):
+    return K * 4 * ((p + 1) * (p + 2) // 2) * 8
+
+def trace(p, K, size=8):
+    return K * 3 * (p + 1) * 4 * size
+
+def buffers(n):
+    return [ctypes.create_string_buffer(n) for _ in range(2)]
+
+VW = (ctypes.c_double * 2)(0.0, 0.0)
+"""
+
+
+def _child(tmp_path, body):
+    src, so, script = (str(tmp_path / n) for n in ("shim.cpp", "shim.so", "child.py"))
+    with open(src, "w") as fh:
+        fh.write(SHIM)
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-o", so, src], check=True)
+    with open(script, "w") as fh:
+        fh.write(PRELUDE + body)
+    r = subprocess.run([sys.executable, script, so, ROOT], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("done"), r.stdout + r.stderr
+
+
+def test_a_batch_needs_no_more_than_its_states(tmp_path):
+    """Room for the states and tables and most of the traces: the batch is made
+    (from its states); with ample room it takes the traces, and gives all back."""
+    _child(tmp_path, r"""
+hs = [context(3, 97, 60), context(1, 83, 41)]
+Ks = [L.dg_num_elements(h) for h in hs]
+assert sum(Ks) >= 16384
+states = sum(3 * state(p, K) for p, K in zip((3, 1), Ks))
+traces = sum(2 * trace(p, K) for p, K in zip((3, 1), Ks))
+before = shim.shim_used()
+b = L.dg_batch_create(hs)
+took = shim.shim_used() - before
+assert states + traces <= took <= states + traces + 65536, (took, states, traces)
+L.dg_batch_destroy(b)
+assert shim.shim_used() == before
+shim.shim_budget(before + states + 65536 + traces * 9 // 10)
+b = L.dg_batch_create(hs)
+assert states <= shim.shim_used() - before <= states + 65536
+L.dg_batch_destroy(b)
+assert shim.shim_used() == before
+shim.shim_budget(before + states // 2)
+try:
+    L.dg_batch_create(hs)
+    raise SystemExit("a batch beyond the memory was made")
+except L.DGError as e:
+    assert e.code == L.DG_ENOMEM
+assert shim.shim_used() == before
+print("done")
+""")
