@@ -23,7 +23,11 @@
  *     data_ptr()); `stream` is a hipStream_t (NULL = default stream).  The
  *     caller owns U, K1 and R; the library owns its operator, geometry and
  *     connectivity tables from dg_setup until dg_destroy, plus one state-
- *     sized scratch buffer used by dg_rk_step.
+ *     sized scratch buffer used by dg_rk_step.  The first multi-step call
+ *     (dg_rk_step, dg_rk_steps, dg_autotune) that is not being captured adds,
+ *     where they leave half of the free memory, face traces (24 (p + 1) values
+ *     per element, 48 q for the over-integrated form) and a second scratch
+ *     state of up to 64 MiB; without them the results are the same.
  *   - Every call returns a dg_status; none aborts or throws across the ABI.
  *     dg_last_error gives the message of the last failing call on a context.
  *   - Calls on one context are not thread-safe; different contexts are

@@ -54,6 +54,8 @@ struct dg_ctx {
   double* d_scratch2 = nullptr;   // a second scratch state (null: an odd number of stages ends with a copy)
   void* d_trace[2] = {nullptr, nullptr};  // face traces of a stage's input and output (null: none)
   size_t trace_size = 0;                  // bytes of each
+  bool no_trace_memory = false, no_scratch2_memory = false;  // found too little memory for them
+  std::vector<void*> retired;             // earlier, smaller trace arrays
   double* h_force = nullptr;        // pinned: partials of the force the host sums
   double* d_force_part = nullptr;
   unsigned* d_force_ticket = nullptr;
@@ -122,6 +124,12 @@ struct StateBuffers {
   }
   bool in_scratch() const { return odd && !S2; }
 };
+// The memory that multi-step calls use and can do without -- face traces and a
+// second scratch state -- is taken by the first call that has a use for it (a
+// context that only serves single stages, or a batch, holds none), unless that
+// call is being captured: it then runs as where the memory is short, from the
+// neighbours' states and with a copy at the end of an odd number of steps.
+void ctx_steps_memory(dg_ctx* c, int nsteps, void* stream);
 // The largest state that gets a second scratch state: beyond it the copy that
 // this saves is 3 % of a step's five stages (20,480 elements at p = 4: 3 of 90
 // us; the smaller the mesh, the more: 5,120 at p = 3: 3 us and a launch of 62).
@@ -131,8 +139,6 @@ constexpr size_t kSecondScratch = (size_t)64 << 20;
 // stages run from the neighbours' states).  A side takes the other's normal flux
 // with the sign changed, so they do not serve a mesh with a periodic seam whose
 // sides have other normals (vertices that are not exact translates).
-// Over-integration switched on after the set-up finds arrays of the nodal size
-// and runs without them.
 inline size_t ctx_trace_bytes(const dg_ctx* c) {
   const int form = ctx_form(c);
   if (!c->mesh.opposed) return 0;

@@ -34,6 +34,8 @@ void free_device(dg_ctx* c) {
                   c->d_cslot, c->d_celem, c->d_cnode, c->d_cface, c->d_cP, c->d_trace[0], c->d_trace[1]};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
+  for (void* p : c->retired) (void)hipFree(p);
+  c->retired.clear();
   if (c->h_cfl) (void)hipHostFree(c->h_cfl);
   if (c->h_force) (void)hipHostFree(c->h_force);
   c->h_cfl = c->h_force = nullptr;
@@ -57,6 +59,7 @@ void free_device(dg_ctx* c) {
   c->d_cP = nullptr;
   c->d_trace[0] = c->d_trace[1] = nullptr;
   c->trace_size = 0;
+  c->no_trace_memory = c->no_scratch2_memory = false;
   c->force_blocks = 0;
   c->dev_ready = false;
 }
@@ -132,6 +135,59 @@ int ctx_fail(dg_ctx* c, int code, const std::string& msg) { return fail(c, code,
 int ctx_hip_fail(dg_ctx* c, hipError_t e, const char* what) { return hip_fail(c, e, what); }
 DeviceTables ctx_tables(const dg_ctx* c) { return tables(c); }
 KernelPhysics ctx_phys(const dg_ctx* c, const double vw[2]) { return kphys(c, vw); }
+
+namespace {
+// Allocation on a context's device inside a call that other threads' stream
+// captures may run beside: in the relaxed mode it neither fails for them nor
+// invalidates them.
+struct AllocationScope {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  int current = -1, device;
+  explicit AllocationScope(int dev) : device(dev) {
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (hipGetDevice(&current) == hipSuccess && current != device) (void)hipSetDevice(device);
+  }
+  ~AllocationScope() {
+    if (current >= 0 && current != device) (void)hipSetDevice(current);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+};
+bool capturing(void* stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  const hipError_t e = hipStreamIsCapturing((hipStream_t)stream, &status);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+}  // namespace
+
+void ctx_steps_memory(dg_ctx* c, int nsteps, void* stream) {
+  const size_t state = (size_t)c->K * 4 * c->ref.Np * sizeof(double);
+  const size_t bytes = traces_pay(c->N, ctx_form(c), c->K, nsteps) ? ctx_trace_bytes(c) : 0;
+  const bool traces = bytes > c->trace_size && !c->no_trace_memory;
+  const bool second = nsteps % 2 != 0 && !c->d_scratch2 && state <= kSecondScratch && !c->no_scratch2_memory;
+  if ((!traces && !second) || capturing(stream)) return;
+  const AllocationScope scope(c->device);
+  if (second && !(leaves_half(state) && hipMalloc((void**)&c->d_scratch2, state) == hipSuccess)) {
+    c->d_scratch2 = nullptr;
+    c->no_scratch2_memory = true;
+    (void)hipGetLastError();
+  }
+  if (traces) {
+    void* tr[2] = {nullptr, nullptr};
+    if (leaves_half(2 * bytes) && hipMalloc(&tr[0], bytes) == hipSuccess && hipMalloc(&tr[1], bytes) == hipSuccess) {
+      // (a captured graph may still use the old ones)
+      for (void* p : c->d_trace)
+        if (p) c->retired.push_back(p);
+      c->d_trace[0] = tr[0];
+      c->d_trace[1] = tr[1];
+      c->trace_size = bytes;
+    } else {
+      if (tr[0]) (void)hipFree(tr[0]);
+      c->no_trace_memory = true;
+      (void)hipGetLastError();
+    }
+  }
+}
 }  // namespace dgmi
 
 extern "C" {
@@ -289,22 +345,6 @@ int dg_setup(dg_ctx* c) {
     return e == hipErrorOutOfMemory ? fail(c, DG_ENOMEM, "device allocation failed")
                                     : hip_fail(c, e, "hipMalloc");
   }
-  // a second scratch state for an odd number of stages; without it they end with a copy
-  if (state <= dgmi::kSecondScratch && hipMalloc((void**)&c->d_scratch2, state) != hipSuccess) {
-    c->d_scratch2 = nullptr;
-    (void)hipGetLastError();
-  }
-  // face traces of a stage's input and output; without the memory for them the
-  // stages run from the neighbours' states
-  if (const size_t bytes = dgmi::ctx_trace_bytes(c)) {
-    if (hipMalloc(&c->d_trace[0], bytes) != hipSuccess || hipMalloc(&c->d_trace[1], bytes) != hipSuccess) {
-      if (c->d_trace[0]) (void)hipFree(c->d_trace[0]);
-      c->d_trace[0] = c->d_trace[1] = nullptr;
-      (void)hipGetLastError();
-    } else {
-      c->trace_size = bytes;
-    }
-  }
   // the allocation-free entry point's static array on this device (a lookup,
   // no allocation); left unset if the lookup fails, which that entry point
   // then reports
@@ -420,6 +460,7 @@ int dg_rk_step(dg_ctx* c, double* U, double* K1, double dt, const double v_w[2],
   std::string err;
   dgmi::DeviceTables t = tables(c);
   dgmi::KernelPhysics k = kphys(c, v_w);
+  dgmi::ctx_steps_memory(c, 1, stream);
   const dgmi::StateBuffers bufs(U, c->d_scratch, c->d_scratch2, 5);
   dgmi::Stages stages = dgmi::ctx_stages(c, 1);
   rc = stages.begin(t, k, U, stream, err);
@@ -447,6 +488,7 @@ int dg_rk_steps(dg_ctx* c, double* U, double* K1, int nsteps, double dt, const d
   const dgmi::DeviceTables t = tables(c);
   const dgmi::KernelPhysics k = kphys(c, v_w);
   const bool walls = !c->mesh.wall_faces.empty();
+  dgmi::ctx_steps_memory(c, nsteps, stream);
   const dgmi::StateBuffers bufs(U, c->d_scratch, c->d_scratch2, 5 * (int64_t)nsteps);
   // the force after step n: its partials by leading waves of step n + 1's
   // first stage launch, whose input is that state, their sum in block order

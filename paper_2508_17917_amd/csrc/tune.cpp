@@ -110,6 +110,7 @@ int dg_autotune(dg_ctx* c, const double* U, int reps, const char* cache_path, vo
   const double vw0[2] = {0.0, 0.0};
   const dgmi::KernelPhysics ph = dgmi::ctx_phys(c, vw0);
   std::string err;
+  dgmi::ctx_steps_memory(c, 2, stream);
   dgmi::Stages stages = dgmi::ctx_stages(c, 2);
   if (e != hipSuccess) rc = dgmi::ctx_hip_fail(c, e, "hipEventCreate");
   if (rc == DG_OK && stages.begin(t, ph, U, s, err) != 0) rc = dgmi::ctx_fail(c, DG_EHIP, err);

@@ -52,6 +52,7 @@ int hipMemcpyAsync(void* d, const void* s, size_t n, int, void*) { memcpy(d, s, 
 int hipMemset(void* d, int v, size_t n) { memset(d, v, n); return 0; }
 int hipMemsetAsync(void* d, int v, size_t n, void*) { memset(d, v, n); return 0; }
 int hipGetDevice(int* d) { *d = 0; return 0; }
+int hipSetDevice(int) { return 0; }
 int hipGetLastError() { return 0; }
 int hipDeviceSynchronize() { return 0; }
 int hipGetSymbolAddress(void** p, const void*) { static double a[1 << 23]; *p = a; return 0; }
@@ -142,5 +143,66 @@ try:
 except L.DGError as e:
     assert e.code == L.DG_ENOMEM
 assert shim.shim_used() == before
+print("done")
+""")
+
+
+def test_a_context_takes_step_memory_with_its_first_steps(tmp_path):
+    """Set-up takes none; a captured call takes none and fails nothing; the first
+    plain call takes the traces and, for an odd number of steps, the second
+    scratch state; a switch to over-integration takes its larger traces; where
+    that would leave less than half of the free memory, nothing is taken and the
+    steps run all the same."""
+    _child(tmp_path, r"""
+base0 = shim.shim_used()
+h = context(4, 67, 64)
+K = L.dg_num_elements(h)
+S, T, TOI = state(4, K), trace(4, K), K * 3 * 7 * 8 * 8
+set_up = shim.shim_used()
+# geometry, connectivity and the CFL work per element, one state, operators
+assert set_up - base0 <= K * (128 + 12 + 48) + S + (1 << 20), set_up - base0
+U, K1 = buffers(S)
+F = ctypes.create_string_buffer(24 * 8)
+
+def steps(n, h=h, U=U, K1=K1):
+    assert lib.dg_rk_steps(h, U, K1, n, 1e-6, VW, F, None) == 0, L.dg_last_error(h)
+
+shim.shim_capturing(1)
+steps(3)
+assert lib.dg_rk_step(h, U, K1, 1e-6, VW, None) == 0
+shim.shim_capturing(0)
+assert shim.shim_used() == set_up
+assert lib.dg_rk_step(h, U, K1, 1e-6, VW, None) == 0   # one step of 8,576 elements: no traces
+assert shim.shim_used() == set_up + S
+steps(2)
+assert shim.shim_used() == set_up + S + 2 * T
+steps(3)
+assert shim.shim_used() == set_up + S + 2 * T
+L.dg_set_overintegration(h, 1)
+steps(2)
+assert shim.shim_used() == set_up + S + 2 * T + 2 * TOI
+L.dg_set_overintegration(h, 0)
+steps(2)
+assert shim.shim_used() == set_up + S + 2 * T + 2 * TOI
+L.dg_destroy(h)
+assert shim.shim_used() == base0
+
+h = context(4, 67, 64)
+for room in (S + S // 2, 2 * S + T):
+    shim.shim_budget(shim.shim_used() + room)
+    for n in (3, 2):
+        before = shim.shim_used()
+        steps(n, h)
+        assert shim.shim_used() - before <= room // 2
+# a refusal stands until the next set-up
+shim.shim_budget(1 << 40)
+before = shim.shim_used()
+steps(3, h)
+assert shim.shim_used() == before
+L.dg_setup(h)
+steps(3, h)
+assert shim.shim_used() == set_up + S + 2 * T
+L.dg_destroy(h)
+assert shim.shim_used() == base0
 print("done")
 """)
