@@ -292,15 +292,19 @@ int dg_newmark_step(double state[3], double F_new, double dt, double M, double C
 int dg_set_tuning(dg_ctx* ctx, int waves, int grid);
 int dg_get_tuning(const dg_ctx* ctx, int* waves, int* grid);
 
-/* Time every launch shape on this context's mesh (two sweeps over the
- * shapes, reps launches of a K1-reading RK stage per shape and sweep, each
- * shape's best kept; reading U, a device state [K][4][Np], writing only
- * library scratch) and keep the fastest.  With cache_path non-NULL, a matching entry of that
- * JSON-lines file (same device architecture, order, precision and element
- * count within a factor 2) is used instead of timing, and a new measurement
- * is appended to it.  Allocates a temporary device register; synchronises
- * `stream`.  *best_us (may be NULL) receives the chosen shape's time per
- * launch in microseconds (0 when taken from the cache). */
+/* Time every launch shape on this context's mesh (two sweeps over the shapes,
+ * reps launches of a K1-reading RK stage per shape and sweep, each shape's best
+ * kept; reading U, a device state [K][4][Np], writing only library scratch) and
+ * keep the fastest; where multi-step calls run from face traces, that kernel's,
+ * and by a quick sweep another shape for the kernel of dg_rhs and dg_rk_stage.  With
+ * cache_path non-NULL, a matching entry of that JSON-lines file (same device
+ * architecture, order, precision, multi-step kernel, with or without curved
+ * elements, and element count within a factor 2) is used instead of timing, and a
+ * new measurement is appended to it; lines of another form are passed over.
+ * Allocates a temporary device register; synchronises `stream`.  *best_us (may be
+ * NULL) receives the time per launch of the multi-step calls' shape in
+ * microseconds (0 when taken from the cache).  dg_set_tuning sets both kernels'
+ * shapes, dg_get_tuning reports the multi-step calls'. */
 int dg_autotune(dg_ctx* ctx, const double* U, int reps, const char* cache_path, void* stream,
                 double* best_us);
 

@@ -25,7 +25,8 @@ constexpr double kRkB[5] = {1432997174477.0 / 9575080441755.0, 5161836677717.0 /
 struct dg_ctx {
   int N = 0;
   int precision = 0;
-  dgmi::StageTuning tune;
+  dgmi::StageTuning tune;         // of the stage from the neighbours' states
+  dgmi::StageTuning tune_traces;  // of the stage from face traces
   dgmi::Physics phys;
   bool have_phys = false;
   std::vector<double> VX, VY;
@@ -97,7 +98,7 @@ struct Stages {
   StageTuning tune;
   void* tr[2];
   int in = 0;
-  Stages(const dg_ctx* c, void* tr0, void* tr1) : N(c->N), form(ctx_form(c)), tune(c->tune), tr{tr0, tr1} {}
+  Stages(const dg_ctx* c, void* tr0, void* tr1) : N(c->N), form(ctx_form(c)), tune(tr0 ? c->tune_traces : c->tune), tr{tr0, tr1} {}
   int begin(const DeviceTables& t, const KernelPhysics& ph, const double* U, void* stream, std::string& err) {
     return tr[0] ? launch_face_traces(N, form, t, ph, U, tr[in], stream, err) : 0;
   }
@@ -162,6 +163,11 @@ inline Stages ctx_stages(const dg_ctx* c, int nsteps) {
   const size_t need = ctx_trace_bytes(c);
   const bool use = need > 0 && need <= c->trace_size && traces_pay(c->N, ctx_form(c), c->K, nsteps);
   return Stages(c, use ? c->d_trace[0] : nullptr, use ? c->d_trace[1] : nullptr);
+}
+// Whether several steps of this context run from traces (or will, once the first
+// of them has taken the memory).
+inline bool steps_from_traces(const dg_ctx* c) {
+  return ctx_trace_bytes(c) > 0 && !c->no_trace_memory && traces_pay(c->N, ctx_form(c), c->K, 2);
 }
 // noalloc.hip: device address of the static scratch array on the current
 // device (looked up once per device); its size in bytes

@@ -18,12 +18,13 @@ pytestmark = [pytest.mark.skipif(not os.path.exists(LIB), reason="libdgmi.so not
               pytest.mark.skipif(shutil.which("g++") is None, reason="no g++")]
 
 SHIM = r"""
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
 static std::map<void*, size_t> blocks;
 static size_t used = 0, budget = (size_t)1 << 40;
-static int capturing = 0, launches = 0;
+static int capturing = 0;
 extern "C" {
 size_t shim_used() { return used; }
 void shim_budget(size_t b) { budget = b; }
@@ -68,9 +69,41 @@ int hipStreamDestroy(void* s) { free(s); return 0; }
 int hipStreamSynchronize(void*) { return 0; }
 int hipStreamIsCapturing(void*, int* c) { *c = capturing; return 0; }
 int hipThreadExchangeStreamCaptureMode(int*) { return 0; }
-int hipLaunchKernel(const void*, unsigned long, unsigned, unsigned long, unsigned, void**, size_t, void*) { ++launches; return 0; }
-int __hipPushCallConfiguration(unsigned long, unsigned, unsigned long, unsigned, size_t, void*) { return 0; }
-int __hipPopCallConfiguration(void*, void*, void*, void*) { return 0; }
+struct Dim { unsigned x, y, z; };
+static Dim cfg[2];
+static std::map<const void*, const char*> names;
+static char trail[1 << 16];
+// the launches since the last call, "kernel grid threads;" each
+const char* shim_launches() { static char out[1 << 16]; strcpy(out, trail); trail[0] = 0; return out; }
+static char last_kernel[512];
+static unsigned last_threads;
+static float (*timer)(const char*, unsigned) = nullptr;
+void shim_timer(float (*f)(const char*, unsigned)) { timer = f; }
+int hipEventElapsedTime(float* ms, void*, void*) { *ms = timer ? timer(last_kernel, last_threads) : 1.0f; return 0; }
+int hipLaunchKernel(const void* f, Dim g, Dim b, void**, size_t, void*) {
+  snprintf(last_kernel, sizeof last_kernel, "%s", names.count(f) ? names[f] : "?");
+  last_threads = b.x;
+  const size_t n = strlen(trail);
+  snprintf(trail + n, sizeof trail - n, "%s %u %u;", last_kernel, g.x, b.x);
+  return 0;
+}
+int __hipPushCallConfiguration(Dim g, Dim b, size_t, void*) { cfg[0] = g; cfg[1] = b; return 0; }
+int __hipPopCallConfiguration(Dim* g, Dim* b, size_t* m, void** s) { *g = cfg[0]; *b = cfg[1]; *m = 0; *s = nullptr; return 0; }
+void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+void __hipRegisterFunction(void**, const void* f, char*, const char* name, unsigned, void*, void*, void*, void*, int*) { names[f] = name; }
+}
+"""
+
+# (the layout of the properties is the runtime's own)
+PROPERTIES = r"""
+#include <cstring>
+#include <hip/hip_runtime_api.h>
+extern "C" hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_t* p, int) {
+  memset((void*)p, 0, sizeof *p);
+  strcpy(p->gcnArchName, "gfx950:test");
+  return hipSuccess;
 }
 """
 
@@ -78,6 +111,7 @@ PRELUDE = r"""
 import ctypes, sys
 shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 shim.shim_used.restype = ctypes.c_size_t
+shim.shim_launches.restype = ctypes.c_char_p
 shim.shim_budget.argtypes = [ctypes.c_size_t]
 sys.path.insert(0, sys.argv[2])
 import meshgen as mg
@@ -106,10 +140,16 @@ VW = (ctypes.c_double * 2)(0.0, 0.0)
 
 
 def _child(tmp_path, body):
-    src, so, script = (str(tmp_path / n) for n in ("shim.cpp", "shim.so", "child.py"))
-    with open(src, "w") as fh:
-        fh.write(SHIM)
-    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-o", so, src], check=True)
+    so, script = str(tmp_path / "shim.so"), str(tmp_path / "child.py")
+    rocm = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")
+    objs = []
+    for name, text in (("shim", SHIM), ("properties", PROPERTIES)):
+        path = str(tmp_path / (name + ".cpp"))
+        with open(path, "w") as fh:
+            fh.write(text)
+        objs.append(str(tmp_path / (name + ".o")))
+        subprocess.run(["g++", "-O1", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I", rocm, "-c", "-o", objs[-1], path], check=True)
+    subprocess.run(["g++", "-shared", "-o", so] + objs, check=True)
     with open(script, "w") as fh:
         fh.write(PRELUDE + body)
     r = subprocess.run([sys.executable, script, so, ROOT], capture_output=True, text=True, timeout=300)
