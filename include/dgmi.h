@@ -304,7 +304,8 @@ int dg_get_tuning(const dg_ctx* ctx, int* waves, int* grid);
  * Allocates a temporary device register; synchronises `stream`.  *best_us (may be
  * NULL) receives the time per launch of the multi-step calls' shape in
  * microseconds (0 when taken from the cache).  dg_set_tuning sets both kernels'
- * shapes, dg_get_tuning reports the multi-step calls'. */
+ * shapes, dg_get_tuning reports the multi-step calls' (waves 2 or 4 also where
+ * they are the default), and to set the reported shape changes neither. */
 int dg_autotune(dg_ctx* ctx, const double* U, int reps, const char* cache_path, void* stream,
                 double* best_us);
 

@@ -192,6 +192,9 @@ int launch_oi_face_traces(int N, const DeviceTables& t, const KernelPhysics& ph,
 int launch_oi_trace_stage(int N, const StageTuning& tune, const DeviceTables& t, const KernelPhysics& ph,
                           const double* U_in, double* U_out, double* K1, double a, double b, double dt,
                           const void* tr_in, void* tr_out, void* stream, std::string& err);
+// the launch shape's waves (2 or 4) that the default is
+int default_trace_waves(int N, int form, int64_t K);
+int default_oi_trace_waves(int N, int64_t K);
 
 // Batched stages over many meshes (one launch per stage).
 struct BatchItem {              // one instance, in device memory

@@ -556,8 +556,7 @@ int launch_oi_trace_n(const StageTuning& tune, const DeviceTables& t, const Kern
                       double* Uout, double* K1, double a, double b, double dt, const void* tr_in, void* tr_out,
                       hipStream_t s, std::string& err) {
   constexpr int BIG = N == 4 ? 8 : 4;
-  const bool few = (t.K + OIOrder<N>::EPT - 1) / OIOrder<N>::EPT <= 4 * device_cus(current_device());
-  if (tune.waves == 2 || (N == 4 && tune.waves == 0 && few))
+  if ((tune.waves ? tune.waves : default_oi_trace_waves(N, t.K)) == 2)
     return launch_oi_trace_w<N, BIG / 2>(tune, t, ph, Uin, Uout, K1, a, b, dt, tr_in, tr_out, s, err);
   return launch_oi_trace_w<N, BIG>(tune, t, ph, Uin, Uout, K1, a, b, dt, tr_in, tr_out, s, err);
 }
@@ -572,6 +571,11 @@ int launch_oi_face_n(const DeviceTables& t, const KernelPhysics& ph, const doubl
   return launch_error(err, "over-integrated face trace launch");
 }
 }  // namespace
+
+int default_oi_trace_waves(int N, int64_t K) {
+  const bool few = (K + OIOrder<4>::EPT - 1) / OIOrder<4>::EPT <= 4 * device_cus(current_device());
+  return N == 4 && few ? 2 : 4;
+}
 
 int launch_oi_trace_stage(int N, const StageTuning& tune, const DeviceTables& t, const KernelPhysics& ph,
                           const double* Uin, double* Uout, double* K1, double a, double b, double dt,

@@ -170,6 +170,10 @@ size_t trace_bytes(int N, int form, int64_t K) {
   return (size_t)K * 3 * (N + 1) * 4 * (form == 2 ? sizeof(float) : sizeof(double));
 }
 
+int default_trace_waves(int N, int form, int64_t K) {
+  return form == kFormOverint ? default_oi_trace_waves(N, K) : TraceOrder<1, double>::WAVES;
+}
+
 int launch_trace_stage(int N, int form, const StageTuning& tune, const DeviceTables& t, const KernelPhysics& ph,
                        const double* Uin, double* Uout, double* K1, double a, double b, double dt,
                        const void* tr_in, void* tr_out, void* stream, std::string& err) {

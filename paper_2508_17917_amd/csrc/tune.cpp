@@ -117,6 +117,10 @@ extern "C" {
 int dg_set_tuning(dg_ctx* c, int waves, int grid) {
   if (!c) return DG_EINVAL;
   if (!valid_shape(waves, grid)) return dgmi::ctx_fail(c, DG_EINVAL, "waves 0/2/4, grid 0..3");
+  // the shape that dg_get_tuning reports changes nothing, whichever shapes (the
+  // default, the autotuner's) the two kernels have
+  int now_waves = 0, now_grid = 0;
+  if (dg_get_tuning(c, &now_waves, &now_grid) == DG_OK && waves == now_waves && grid == now_grid) return DG_OK;
   c->tune.waves = waves;
   c->tune.grid = grid;
   c->tune_traces = c->tune;
@@ -125,8 +129,11 @@ int dg_set_tuning(dg_ctx* c, int waves, int grid) {
 
 int dg_get_tuning(const dg_ctx* c, int* waves, int* grid) {
   if (!c || !waves || !grid) return DG_EINVAL;
-  const dgmi::StageTuning& t = dgmi::steps_from_traces(c) ? c->tune_traces : c->tune;
-  *waves = t.waves ? t.waves : (c->overint ? 2 : dgmi::default_waves(c->N, c->precision));
+  const bool traces = dgmi::steps_from_traces(c);
+  const dgmi::StageTuning& t = traces ? c->tune_traces : c->tune;
+  *waves = t.waves ? t.waves
+                   : (traces ? dgmi::default_trace_waves(c->N, dgmi::ctx_form(c), c->K)
+                             : (c->overint ? 2 : dgmi::default_waves(c->N, c->precision)));
   *grid = t.grid;
   return DG_OK;
 }

@@ -81,3 +81,39 @@ h3 = context(4, 67, 64, precision=2)
 assert tune(h3, path) == 0.0 and L.dg_get_tuning(h3)[0] == 2
 print("done")
 """)
+
+
+def test_the_reported_shape_changes_nothing(tmp_path):
+    """dg_set_tuning(dg_get_tuning()) on every order and form, nodal and over-
+    integrated, on meshes that fill the chip and that do not: the same launches
+    of right-hand sides and steps as before, by default, after a shape was set
+    and after the autotuner picked one a kernel.  Another shape does change them."""
+    _child(tmp_path, SHAPES + r"""
+FN = ctypes.CFUNCTYPE(ctypes.c_float, ctypes.c_char_p, ctypes.c_uint)
+timer = FN(lambda name, threads: 1.0 if threads == (128 if b"trace" in name else 256) else 2.0)
+shim.shim_timer(timer)
+for nt, nr in ((9, 5), (101, 99)):
+    mesh = mg.ogrid(nt, nr, 0.5, 5.0, 1.01)
+    for p, precision, oi in [(p, f, 0) for p in (1, 4, 6) for f in (0, 2, 3)] + [(p, 0, 1) for p in (3, 4, 5)]:
+        h = context(p, nt, nr, precision, mesh)
+        L.dg_set_overintegration(h, oi)
+        big = buffers(state(p, 2 * nt * nr))
+        U, K1 = big
+        for how in ("default", "set", "tuned"):
+            if how == "set":
+                L.dg_set_tuning(h, 2, 1)
+                assert L.dg_get_tuning(h) == (2, 1)
+            if how == "tuned":
+                tune(h)
+            before = rhs(h), steps(h)
+            L.dg_set_tuning(h, *L.dg_get_tuning(h))
+            assert (rhs(h), steps(h)) == before, (nt, p, precision, oi, how)
+        if oi and nr == 99:
+            L.dg_set_tuning(h, 0, 0)
+            w = L.dg_get_tuning(h)[0]
+            default = steps(h)
+            L.dg_set_tuning(h, 6 - w, 0)   # the other of 2 and 4
+            assert steps(h) != default
+        L.dg_destroy(h)
+print("done")
+""")
