@@ -37,3 +37,31 @@ def test_fused_training_block_edges(n_out, B):
     got = _unpack(g, n_out=n_out)
     for k in go:
         assert _rel(got[k], go[k]) <= 3e-2, k
+
+
+@pytest.mark.parametrize("n_out,B", [(24, 16385), (32, 20001), (17, 49217), (24, 65), (17, 97), (60, 16449)])
+def test_fused_training_last_block_decides(n_out, B):
+    """The samples of the last, partly filled block carry nearly all of the loss
+    and gradient (their targets are ten thousand standard deviations off, the
+    others' one): a sample of it left out, or a row past the end counted, is far
+    outside the bounds, which are those of a batch of one."""
+    torch = _torch()
+    from paper_2508_17917_amd import _lib as L
+    params, X, T, norm = _net_case(7, B=B, n_out=n_out)
+    tail = (B - 1) % 64 + 1
+    rng = np.random.default_rng(B)
+    T[-tail:] = norm[2] + 1e4 * norm[3] * rng.standard_normal((tail, n_out)).astype(T.dtype)
+    q, Xn, Tn = _oracle_inputs(params, X, T, norm, n_out=n_out)
+    lo, go = OC.loss_and_grads(q, Xn, Tn)
+    rest, _ = OC.loss_and_grads(q, Xn[:-tail], Tn[:-tail])
+    assert rest * (B - tail) < 0.05 * lo * B   # (what the case is for)
+    m = L.dg_mlp_create(28, 128, n_out, B)
+    L.dg_mlp_set_params(m, params)
+    L.dg_mlp_set_normalization(m, *norm)
+    _say("fused training tail n_out=%d B=%d" % (n_out, B))
+    loss = L.dg_mlp_backward(m, torch.from_numpy(X).cuda(), torch.from_numpy(T).cuda())
+    got = _unpack(L.dg_mlp_get_grad(m), n_out=n_out)
+    L.dg_mlp_destroy(m)
+    assert abs(loss - lo) <= 3e-2 * lo
+    for k in go:
+        assert _rel(got[k], go[k]) <= 3e-2, k
