@@ -373,17 +373,25 @@ static int batch_build(dg_batch* b, dg_ctx* const* ctxs, int n) {
       (e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking)) != hipSuccess)
     return bhip(b, e, "allocating batch tables");
   // face traces last, the batch runs without them: where they serve every
-  // instance, the step's extra launch pays and they leave half of what is free
+  // instance, pay and leave half of what is free.  They pay from 16,384 elements
+  // on, where every instance is of order 3 or 4 from 32,768 on (us a step, states
+  // -> traces, best shape of each, n instances of one order): 8,192 elements, n = 2:
+  // p = 1 FP64 62 -> 65, p = 4 79 -> 87, FP32 64 -> 69; 16,384, n = 2: p = 1 94 -> 80,
+  // p = 2 105 -> 102, p = 3 112 -> 114, p = 4 123 -> 126, FP32 89 -> 92, p = 6 206 ->
+  // 185; 16,384 to 28,672, n = 16, p = 3 and 4: 126 -> 144, 130 -> 144, 107 -> 123
+  // (FP32), 172 -> 173; 32,768, n = 16: p = 3 213 -> 192, p = 4 226 -> 210, FP32 145 ->
+  // 130 and 156 -> 145, n = 64 257 -> 252 and 270 -> 257.
   int64_t elements = 0, stage = 0;
   size_t traces = 0;
-  bool served = b->form <= 2;
+  bool served = b->form <= 2, orders34 = true;
   for (int i = 0; i < n; ++i) {
     elements += ctxs[i]->K;
     stage += dgmi::trace_stage_bytes(ctxs[i]->N, b->form, ctxs[i]->K);
     traces += 2 * dgmi::trace_bytes(ctxs[i]->N, b->form, ctxs[i]->K);
     served = served && dgmi::ctx_trace_bytes(ctxs[i]) > 0;
+    orders34 = orders34 && (ctxs[i]->N == 3 || ctxs[i]->N == 4);
   }
-  if (served && elements >= 16384 && dgmi::leaves_half(traces)) {
+  if (served && elements >= (orders34 ? 32768 : 16384) && dgmi::leaves_half(traces)) {
     b->tr.assign(2 * n, nullptr);
     for (int i = 0; i < 2 * n; ++i)
       if (hipMalloc(&b->tr[i], dgmi::trace_bytes(ctxs[i / 2]->N, b->form, ctxs[i / 2]->K)) != hipSuccess) {

@@ -146,7 +146,7 @@ inline size_t ctx_trace_bytes(const dg_ctx* c) {
   if (!c->mesh.celem.empty() && (form == kFormOverint || beyond_cache(trace_stage_bytes(c->N, form, c->K)))) return 0;
   return trace_bytes(c->N, form, c->K);
 }
-// Whether nsteps steps on K elements (of one mesh or a batch) run from traces:
+// Whether nsteps steps on K elements of one mesh run from traces:
 // the launch that makes the first ones costs 6 us on a small mesh, which the
 // five stages of a single step win back from about 16,000 elements on (one
 // step at p = 4 FP32: 8,192 elements 59.3 against 56.2 us, 20,480 93.9 against

@@ -246,3 +246,30 @@ L.dg_destroy(h)
 assert shim.shim_used() == base0
 print("done")
 """)
+
+
+def test_a_batch_takes_traces_where_they_pay(tmp_path):
+    """From 16,384 elements on; where all instances are of order 3 or 4, 32,768."""
+    _child(tmp_path, r"""
+small, large = mg.ogrid(91, 45, 0.5, 5.0, 1.02), mg.ogrid(97, 86, 0.5, 5.0, 1.02)   # 8,190 and 16,684
+def traces(*what):
+    hs = [context(p, 0, 0, f, m) for p, m, f in what]
+    Ks = [L.dg_num_elements(h) for h in hs]
+    before = shim.shim_used()
+    b = L.dg_batch_create(hs)
+    extra = shim.shim_used() - before - sum(3 * state(p, K) for (p, m, f), K in zip(what, Ks))
+    L.dg_batch_destroy(b)
+    want = sum(2 * trace(p, K, 4 if f == 2 else 8) for (p, m, f), K in zip(what, Ks))
+    for h in hs:
+        L.dg_destroy(h)
+    assert extra < 65536 or want <= extra < want + 65536
+    return extra >= 65536
+for f in (0, 2):
+    for p in (1, 2, 5, 6):
+        assert not traces((p, small, f), (p, small, f)) and traces((p, large, f))
+    for p in (3, 4):
+        assert not traces((p, large, f), (p, small, f)) and traces((p, large, f), (7 - p, large, f))
+        assert traces((p, small, f), (2, large, f))
+assert not traces((4, large, 3), (4, large, 3))   # bfloat16 operators
+print("done")
+""")

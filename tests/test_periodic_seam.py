@@ -70,7 +70,7 @@ def test_batch_with_such_a_mesh():
     torch = _torch()
     meshes = [_wavy(5e-9, (90, 70)), mg.ogrid(71, 53, 0.5, 8.0, 1.02)]
     print("[gpu-case] seam batch", flush=True)
-    b, solvers, states = _batch_case(torch, (3, 3), meshes, 2, 5)
+    b, solvers, states = _batch_case(torch, (3, 2), meshes, 2, 5)
     assert sum(s.K for s in solvers) >= 16384
     dt, vw = np.full(2, 1e-6), np.zeros((2, 2))
     for i in range(2):
