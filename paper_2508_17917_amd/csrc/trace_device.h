@@ -24,11 +24,11 @@
 // elements (in brackets 327,680): p = 1 FP64 18.2 -> 15.1 (255 -> 137), p = 2 FP64
 // 20.6 -> 17.9 (286 -> 191), p = 4 FP32 18.5 -> 15.9 (228 -> 203) and FP64 25.7 ->
 // 22.1, p = 5 FP32 39 -> 28, p = 6 FP32 37 -> 31.6 and FP64 73 -> 50.  What bounds
-// it: on 20,480 elements the vector unit's issue (about 1,000 instructions a
-// tile, five tiles a SIMD, 85 % of the time three waves are resident) between a
-// launch's 2.5 us and 3,000 cycles of cold first loads; beyond the last-level
-// cache memory (p = 4 FP32: 0.95 GB a stage at 4.5 TB/s, 92 % of a large copy's
-// rate).
+// it: on 20,480 elements the issue and latency of a few waves per SIMD (p = 4 FP32:
+// 870 vector and 36 matrix instructions a tile, five tiles a SIMD; a wave waits
+// for memory, LDS or its turn in two thirds of its cycles) after a launch's cold first
+// loads; beyond the last-level cache memory (p = 4 FP32: 0.95 GB a stage at 4.5
+// TB/s, 92 % of a large copy's rate).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -200,7 +200,8 @@ __device__ __forceinline__ void fetch_gradient(const T (&gxk)[TraceOrder<N, T, L
 
 // Zero the pad columns of `rows` rows of RS values.  The matrix-core products
 // read them against zero operator entries, and 0 times a NaN or an infinity is
-// not 0: a row is one element's, its pads must be no other's.
+// not 0: a row is one element's, its pads must be no other's.  (Per tile: 0.994 to
+// 1.008 of the steps' times with the pads cleared once a launch.)
 template <int N, typename T>
 __device__ __forceinline__ void zero_pads(T* rows0, int rows, int lane) {
   using P = TraceOrder<N, T>;
@@ -214,7 +215,9 @@ __device__ __forceinline__ void zero_pads(T* rows0, int rows, int lane) {
 // The traces of the states staged in sU (synced): one lane per face node of
 // the tile's nel elements.  Boundary faces carry the wall's or the far field's
 // viscous flux, and the ghost's norm in the maximum.  skip: the slots (bits) whose
-// traces another wave writes; their new states are not in sU.
+// traces another wave writes: their new states are not in sU, and what is formed
+// of those rows stays in them (left out before the norm, 4 us of 990 slower at
+// p = 4 FP32).
 template <int N, typename T, bool PERT, bool LARGE>
 __device__ __forceinline__ void write_traces(const FaceConst<T>& fc, const FaceLane<N, T, LARGE>& fl,
                                              const T* sU, const T* sGeo, T* sNorm, const T* sFrag,
@@ -225,7 +228,7 @@ __device__ __forceinline__ void write_traces(const FaceConst<T>& fc, const FaceL
   tile_gradient<N, T, LARGE>(sU, sGeo, sFrag, lane, nel, gxk, gyk);
   T gxp[4], gyp[4];
   fetch_gradient<N, T, LARGE>(gxk, gyk, fl.e, fl.n, gxp, gyp);
-  const bool ok = lane < nel * P::NF && !((skip >> fl.e) & 1);
+  const bool ok = lane < nel * P::NF;
   T vn[4] = {T(0), T(0), T(0), T(0)};
   T nrm = T(0);
   if (ok) {
@@ -258,7 +261,7 @@ __device__ __forceinline__ void write_traces(const FaceConst<T>& fc, const FaceL
     sNorm[lane] = nrm;
   }
   wave_sync();
-  if (ok) {
+  if (ok && !((skip >> fl.e) & 1)) {
     T gmax = T(0);
 #pragma unroll
     for (int jj = 0; jj < P::Nfp; ++jj) {
