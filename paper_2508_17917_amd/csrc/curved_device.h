@@ -24,9 +24,7 @@ namespace dgmi {
 // A curved wave is one chain of dependent phases, the longest in a launch, so
 // what it waits for is loaded ahead: the three neighbours' states with the own
 // one (in LDS until the face terms take their place), the operators' rows eight
-// at a time, K1 before the product with P.  p = 4, 160 such elements: 37,200
-// cycles a wave with four rows at a time and the neighbours' values from global
-// memory, 31,500 so (13 us of a launch).
+// at a time, K1 before the product with P.
 constexpr int curved_face_doubles(int N) {  // neighbours' states, later the face terms
   return 36 * (N + 1) > 6 * (N + 1) * (N + 2) ? 36 * (N + 1) : 6 * (N + 1) * (N + 2);
 }

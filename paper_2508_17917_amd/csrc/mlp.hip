@@ -449,9 +449,10 @@ struct TrainShape {
 // 42 us.  With four waves of two tiles each, every lane's instructions in one
 // chain, 60 us; with transposed copies written value by value, the transposed
 // weights gathered by eight 2-byte reads an operand and the bias sums left to
-// one wave, 66 us.  Bound by vector issue: 64 GELU pairs a lane and block, each
-// of 21 instructions, two of them quarter-rate, are 60 % of it; the
-// matrix products are 4.4 of about 27 thousand cycles a block and SIMD.
+// one wave, 66 us.  Bound by one chain of issue and latency a wave: of its 39,800
+// cycles a block, 2,170 vector instructions (64 GELU pairs of 21, two of them
+// quarter-rate, are 60 % of them) and 2,180 cycles of matrix products, and in
+// 47 % it waits for LDS and the other waves.
 template <int KIT, int HT, int OT, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void train_kernel(
     TrainArgs g) {

@@ -16,9 +16,9 @@
 // us a stage on 20,480 elements, that stage -> this: p = 1 21.5 -> 15.4, p = 2
 // 25.7 -> 21.6, p = 3 45.6 -> 27.1, p = 4 89.4 -> 54.2, p = 5 186.6 -> 113.2, p = 6
 // 404 -> 346.  Bound by the FP64 units, which the matrix and the vector
-// instructions share: at p = 4 84 matrix instructions of 64 cycles (a quarter of
-// their rows idle: three of four element slots) and about 1,200 vector
-// instructions of 4 a tile, 6.7 tiles a SIMD.
+// instructions share: at p = 4 78 matrix instructions of 64 cycles (a quarter of
+// their rows idle: three of four element slots) and 1,440 vector instructions of
+// 4 and more a tile, 6.7 tiles a SIMD.
 #include <hip/hip_runtime.h>
 
 #include "trace_device.h"

@@ -10,8 +10,8 @@ namespace dgmi {
 // the curved set (CURVED: one element per wave, with its traces), then the wall
 // force of the input state and the sum of the previous partials.  20,320 straight
 // elements and 160 of the set, p = 4 FP32: 21.4 us a stage from the neighbours'
-// states, 19.7 from traces; then the curved waves, about 15 us of one chain each,
-// and the straight tiles beside them take about as long.
+// states, 19.7 from traces; the longest then is a curved wave's chain of dependent
+// phases, with the straight tiles beside it.
 template <int N, typename T, bool CURVED>
 constexpr int wave_lds(int tile_size) {
   const int curved = (int)((curved_lds_doubles(N) + 1) * sizeof(double) / sizeof(T));
